@@ -62,11 +62,11 @@ namespace {
 constexpr int kMaxN = 1024;
 constexpr int kMinN = 8;
 
-// n = 2^a or 3 * 2^a: radix plan with radices up to `maxr` (8 or 4), 4 bits
-// per stage, first stage lowest (the kernels' compile-time plans, plan_radix,
-// are the same); the radix-3 stage comes last so that the sub-transform
-// length before every stage is a power of two.
-bool radix_plan(int n, uint32_t* rad, int* nst, int maxr = 8) {
+// n = 2^a or 3 * 2^a: radix plan, 4 bits per stage, first stage lowest (the
+// kernels' compile-time plans, plan_radix, are the same).  The factor 3 sits in
+// the middle stage of three (a >= 4) or in a last one, so that the
+// sub-transform length before every stage but the last is a power of two.
+bool radix_plan(int n, uint32_t* rad, int* nst) {
   if (n < kMinN || n > kMaxN || (n & 1)) return false;
   std::vector<int> r;
   int m = n;
@@ -75,10 +75,14 @@ bool radix_plan(int n, uint32_t* rad, int* nst, int maxr = 8) {
   if (m & (m - 1)) return false;
   int a = 0;
   while ((1 << a) < m) ++a;
-  if (maxr == 8) {
+  const int q = a / 3, rem = a % 3;
+  if (three && a >= 4) {
+    // 48: 4 3 4, 96: 4 6 4, 192: 8 3 8, 384: 8 6 8, 768: 8 12 8
+    const int e = a >= 6 ? 3 : 2;
+    r = {1 << e, 3 << (a - 2 * e), 1 << e};
+  } else {
     // radix 8, the remainder as 4 .. 4 (a = 3q + 1) or a radix-4 second stage
     // (a = 3q + 2), so that the plan starts and ends with the same radix
-    const int q = a / 3, rem = a % 3;
     if (rem == 0) {
       for (int i = 0; i < q; ++i) r.push_back(8);
     } else if (rem == 1) {
@@ -98,12 +102,8 @@ bool radix_plan(int n, uint32_t* rad, int* nst, int maxr = 8) {
         for (int i = 0; i < q - 1; ++i) r.push_back(8);
       }
     }
-  } else {
-    const int q = a / 2, rem = a % 2;
-    if (rem == 1) r.push_back(2);
-    for (int i = 0; i < q; ++i) r.push_back(4);
+    if (three) r.push_back(3);
   }
-  if (three) r.push_back(3);
   *rad = 0;
   for (size_t i = 0; i < r.size(); ++i) *rad |= uint32_t(r[i]) << (4 * i);
   *nst = int(r.size());
@@ -136,10 +136,6 @@ int ilog2(int v) {
 }
 
 bool threads_ok(int t) { return t == 64 || t == 128 || t == 256 || t == 512; }
-
-// Column launches at these lengths take an instance whose FFT stages run in
-// place (a compile-time power-of-two plan).
-bool col_in_place(int ny) { return kernels_have_length(ny, true) && (ny & (ny - 1)) == 0; }
 
 // A row tile of rt rows (rt even, dividing ny) fits the LDS limit and leaves
 // at most kMaxPer pointwise elements per thread.
@@ -329,20 +325,19 @@ qpat_status exec_build(Exec& E, const std::vector<Item>& items) {
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
       cus = 0;
-    E.row_tg = u && cus > 0 && kernels_have_length(m0.nx, false) && ni * E.row_ntile <= 2 * cus;
-    E.col_tg = u && cus > 0 && kernels_have_length(m0.ny, true) && ni * E.col_ntile <= 2 * cus;
-    // row instances with a compile-time length, and column instances with a
-    // compile-time power-of-two length, run in place unless they read global
-    // twiddles (one LDS line buffer instead of two)
-    if (u) E.row_lds = row_lds_bytes(m0.nx, m0.rt, E.row_tg, kernels_have_length(m0.nx, false) && !E.row_tg);
-    if (u) E.col_lds = col_lds_bytes(m0.ny, m0.ct, E.col_tg, col_in_place(m0.ny) && !E.col_tg);
+    E.row_tg = u && cus > 0 && kernels_have_length(m0.nx) && ni * E.row_ntile <= 2 * cus;
+    E.col_tg = u && cus > 0 && kernels_have_length(m0.ny) && ni * E.col_ntile <= 2 * cus;
+    // instances with a compile-time length run in place unless they read
+    // global twiddles (one LDS line buffer instead of two)
+    if (u) E.row_lds = row_lds_bytes(m0.nx, m0.rt, E.row_tg, kernels_have_length(m0.nx) && !E.row_tg);
+    if (u) E.col_lds = col_lds_bytes(m0.ny, m0.ct, E.col_tg, kernels_have_length(m0.ny) && !E.col_tg);
   }
-  if (!E.uniform && E.tab_nx && kernels_have_length(E.tab_nx, false)) {
+  if (!E.uniform && E.tab_nx && kernels_have_length(E.tab_nx)) {
     E.row_lds = 0;
     for (int i = 0; i < ni; ++i)
       E.row_lds = std::max(E.row_lds, row_lds_bytes(items[i].m.nx, items[i].m.rt, false, true));
   }
-  if (!E.uniform && E.tab_ny && col_in_place(E.tab_ny)) {
+  if (!E.uniform && E.tab_ny && kernels_have_length(E.tab_ny)) {
     E.col_lds = 0;
     for (int i = 0; i < ni; ++i)
       E.col_lds = std::max(E.col_lds, col_lds_bytes(items[i].m.ny, items[i].m.ct, false, true));
@@ -754,13 +749,12 @@ qpat_status plan_build(qpat_plan P, const double* c0, const double* rho0) {
   // the earlier radices), stored as [stage][r - 1][k]; the stage blocks
   // telescope to n - R0 entries.
   // rev: the plan in reverse order (the inverse transforms of the fused
-  // column passes; power-of-two lengths only, Ns stays a power of two).
+  // column passes).
   auto twid = [](int n, bool rev) {
     uint32_t rad = 0;
     int nst = 0;
-    radix_plan(n, &rad, &nst, 8);
+    radix_plan(n, &rad, &nst);
     std::vector<float2> t(n, make_float2(0.f, 0.f));
-    if (rev && (n & (n - 1))) return t;
     auto radix = [&](int st) { return int((rad >> (4 * (rev ? nst - 1 - st : st))) & 15); };
     const int r0 = radix(0);
     int ns = 1;
@@ -789,7 +783,7 @@ qpat_status plan_build(qpat_plan P, const double* c0, const double* rho0) {
 
   // ---- upload (host checks are done; from here on a device is needed)
   {
-    const hipError_t e = kernels_allow_lds(kMaxLds);
+    const hipError_t e = kernels_allow_lds(nx, ny, kMaxLds);
     if (e != hipSuccess) return fail(QPAT_E_HIP, std::string("LDS attribute: ") + hipGetErrorString(e));
   }
   Carver cv;
@@ -847,8 +841,8 @@ qpat_status plan_build(qpat_plan P, const double* c0, const double* rho0) {
   M.lossy = lossy ? 1 : 0;
   M.dt = float(dt);
   M.ypow = float(p.y);
-  radix_plan(nx, &M.radx, &M.nstx, 8);
-  radix_plan(ny, &M.rady, &M.nsty, 8);
+  radix_plan(nx, &M.radx, &M.nstx);
+  radix_plan(ny, &M.rady, &M.nsty);
   M.c2 = (const float*)(d + o_c2);
   M.c2eta = (const float*)(d + o_c2eta);
   M.c2tau = (const float*)(d + o_c2tau);

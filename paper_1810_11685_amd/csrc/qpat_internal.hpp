@@ -36,7 +36,7 @@ struct Medium {
   int lrt, lct;           // log2(rt), log2(ct)
   int srt, lsrt;          // spectra are stored in srt x ct tiles (srt a multiple of rt); log2(srt)
   int rthr, cthr;         // threads per block of the row / column passes
-  uint32_t radx, rady;    // radix plans (max radix 8), 4 bits per stage, first stage lowest
+  uint32_t radx, rady;    // radix plans, 4 bits per stage, first stage lowest
   int nstx, nsty;
   const float *c2, *c2eta, *c2tau, *rho0, *bx, *by;   // [ny][nx]; bx = dt/rho_x, by = dt/rho_y
   const float *avx, *arx, *avy, *ary;                 // PML diagonals: [nx] / [ny]
@@ -153,11 +153,12 @@ hipError_t launch_col(int cm, int mcode, const Launch& L, bool uniform, int len,
 // Row lengths whose RM_FZ instances exist (uniform launches, and table
 // launches of that length), for launches reading global twiddles (tg) or not.
 bool kernels_row_fused(int n, bool tg);
-// Row (col false) or column lengths with compile-time kernel instances.
-bool kernels_have_length(int n, bool col);
+// Row and column lengths with compile-time kernel instances.
+bool kernels_have_length(int n);
 hipError_t launch_combine(const Item* items, const IO* io, int nitems, int max_count,
                           hipStream_t st);
-hipError_t kernels_allow_lds(size_t bytes);
+// Let the pass kernels that an nx x ny grid can launch use `bytes` of dynamic LDS.
+hipError_t kernels_allow_lds(int nx, int ny, size_t bytes);
 hipError_t launch_tap_order(const Item* items, const IO* io, int nitems, int max_count, hipStream_t st);
 hipError_t launch_grad_c(const float* c2, const float* p0, const float* g0, const double* gc, long long n,
                          int batch, long long gc_stride, float* out, hipStream_t st);
