@@ -184,7 +184,9 @@ qpat_status qpat_medium_grad_bytes(qpat_plan plan, int32_t interval, int32_t bat
 qpat_status qpat_medium_grad(qpat_plan plan, const float* p0, const float* res, int32_t interval, void* work,
                              float* grad_p0, float* grad_c, int32_t batch, qpat_stream stream);
 
-/* Launch shape of the FFT passes: rows per row-pass block, spectrum columns
+/* Launch shape of the FFT passes, chosen per batch size until qpat_set_tiles
+ * or qpat_tune fixes it (qpat_get_tiles then gives the shape of one vector;
+ * results do not depend on it): rows per row-pass block, spectrum columns
  * per column-pass block (powers of two dividing ny and nx/2; rows even, and at
  * most ny/8 when ny is a power of two of 128 or more) and
  * threads per block of each pass (64, 128, 256 or 512; rows*nx at most 8 and

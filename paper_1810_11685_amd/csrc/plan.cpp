@@ -122,13 +122,6 @@ double stability_limit(double cmax, double cref, double dx, double dy) {
   return 2.0 * std::asin(cref / cmax) / (cref * kmax);
 }
 
-int pow2_floor(int v) {
-  int p = 1;
-  while (p * 2 <= v) p *= 2;
-  return p;
-}
-int pow2_divisor(int v) { return v & (-v); }
-
 int ilog2(int v) {
   int l = 0;
   while ((1 << l) < v) ++l;
@@ -172,9 +165,58 @@ int storage_rows(int ny, int rt) {
   return s;
 }
 
-// Defaults: small tiles (many blocks) with enough threads to keep every
-// thread busy in the radix-8 stages.
-void default_tiles(int nx, int ny, int* rt, int* ct, int* rthr, int* cthr) {
+int pow2_ceil(int v) {
+  int p = 1;
+  while (p < v) p *= 2;
+  return p;
+}
+
+// Launch shape for b vectors of a plan in one launch, until
+// qpat_set_tiles or qpat_tune fixes one: two rows / one column a block, the
+// most blocks a pass can have, growing while
+//  - blocks are shorter than 192 elements and there are more than one per CU, or
+//  - there are more than kManyBlocks (two per CU, the line between global and
+//    LDS twiddles) and a row block is shorter than 1536 elements, or
+//  - there are more than eight per CU and a block of short columns (256 or
+//    fewer) has at most 512 elements (1024 x 256 x 16: one column a block
+//    147 us, four 140);
+// then one thread an element where a pass has at most kManyBlocks (a block's
+// chain of dependent stages bounds it), eight elements a row thread and four a
+// column thread above (more blocks share a CU).  Measured in us per iterate of
+// a forward + adjoint pair, before -> now, the tuner's best shape behind:
+// 64^2 33 -> 24 (24), 128^2 37.4 -> 24.3 (24.3), 128^2 x 8 36.9 -> 25.4 (24.5),
+// 256^2 37.8 -> 26.8 (26.8), 512^2 41.5 -> 35.5 (35.5), 512^2 x 2 49.9 -> 46.1
+// (46.1), 1024^2 73.0 -> 70.5 (70.5); 512^2 x 8 and 1024^2 x 8 as before.
+constexpr int kManyBlocks = 512;
+void auto_tiles(int nx, int ny, int b, int* rt, int* ct, int* rthr, int* cthr) {
+  const int64_t cus = kManyBlocks / 2;
+  int r = 2;
+  auto rblocks = [&] { return int64_t(b) * (ny / r); };
+  while (((r * nx < 192 && rblocks() > cus) || (r * nx < 1536 && rblocks() > kManyBlocks)) &&
+         row_tile_ok(nx, ny, 2 * r, kMaxThreads))
+    r *= 2;
+  int rh = std::max(64, std::min(kMaxThreads, pow2_ceil(rblocks() <= kManyBlocks ? r * nx : r * nx / 8)));
+  while (rh < kMaxThreads && !row_tile_ok(nx, ny, r, rh)) rh *= 2;
+  int c = 1;
+  auto cblocks = [&] { return int64_t(b) * (nx / 2 / c); };
+  while (((c * ny < 192 && cblocks() > cus) || (ny <= 256 && 2 * c * ny <= 1024 && cblocks() > 8 * cus)) &&
+         col_tile_ok(nx / 2, ny, 2 * c, kMaxThreads))
+    c *= 2;
+  int ch = std::max(128, std::min(kMaxThreads, pow2_ceil(cblocks() <= kManyBlocks ? c * ny : c * ny / 4)));
+  while (ch < kMaxThreads && !col_tile_ok(nx / 2, ny, c, ch)) ch *= 2;
+  *rt = r;
+  *ct = c;
+  *rthr = rh;
+  *cthr = ch;
+}
+
+// Launch shape of a problem in a table launch (a batch of problems): blocks of
+// about 2048 elements, 256 threads, whatever the number of problems.  A launch
+// over several grid sizes runs with the largest thread count and LDS of its
+// problems, so small blocks of 512 threads cost it (7 problems of 256^2 to
+// 512^2 in one launch set: 25.5 ms, with the shapes above 37.5; one launch
+// sequence per size: 22.8 either way).
+void table_tiles(int nx, int ny, int* rt, int* ct, int* rthr, int* cthr) {
   int r = 2;
   while (r < 16 && r * nx < 2048 && row_tile_ok(nx, ny, 2 * r, 256)) r *= 2;
   int rthr_ = 64;
@@ -187,6 +229,18 @@ void default_tiles(int nx, int ny, int* rt, int* ct, int* rthr, int* cthr) {
   *ct = c;
   *rthr = rthr_;
   *cthr = cthr_;
+}
+
+// The launch shape as the kernels read it.
+void shape_medium(Medium& m, int rt, int ct, int rthr, int cthr) {
+  m.rt = rt;
+  m.ct = ct;
+  m.lrt = ilog2(rt);
+  m.lct = ilog2(ct);
+  m.srt = storage_rows(m.ny, rt);
+  m.lsrt = ilog2(m.srt);
+  m.rthr = rthr;
+  m.cthr = cthr;
 }
 
 }  // namespace
@@ -506,7 +560,19 @@ struct qpat_plan_s {
     grad_execs.clear();
   }
   bool graph = false;
-  int rt = 2, ct = 1, rthr = kBlock, cthr = kBlock;
+  bool auto_shape = true;   // the launch shape follows the batch size until set_tiles / tune
+  int rt = 2, ct = 1, rthr = kBlock, cthr = kBlock;   // the fixed shape (auto: the one of a single vector)
+  // the medium with the launch shape for b vectors (b = 0: for a table launch)
+  Medium medium_for(int b) const {
+    Medium m = med;
+    if (auto_shape) {
+      int r, c, rh, ch;
+      if (b > 0) auto_tiles(prm.nx, prm.ny, b, &r, &c, &rh, &ch);
+      else table_tiles(prm.nx, prm.ny, &r, &c, &rh, &ch);
+      shape_medium(m, r, c, rh, ch);
+    }
+    return m;
+  }
   // opt-in output check: flag set by a kernel after each solve
   bool check = false;
   int* d_flag = nullptr;
@@ -868,15 +934,8 @@ qpat_status plan_build(qpat_plan P, const double* c0, const double* rho0) {
   M.node_off = (const int*)(d + o_snoff);
   M.nodes = (const int4*)(d + o_snodes);
   M.scon = (const int*)(d + o_scon);
-  default_tiles(nx, ny, &P->rt, &P->ct, &P->rthr, &P->cthr);
-  M.rt = P->rt;
-  M.ct = P->ct;
-  M.rthr = P->rthr;
-  M.cthr = P->cthr;
-  M.lrt = ilog2(P->rt);
-  M.lct = ilog2(P->ct);
-  M.srt = storage_rows(ny, P->rt);
-  M.lsrt = ilog2(M.srt);
+  auto_tiles(nx, ny, 1, &P->rt, &P->ct, &P->rthr, &P->cthr);
+  shape_medium(M, P->rt, P->ct, P->rthr, P->cthr);
   return QPAT_OK;
 }
 
@@ -938,8 +997,9 @@ qpat_status plan_exec(qpat_plan P, int b, Exec** out) {
   auto it = P->execs.find(b);
   if (it == P->execs.end()) {
     std::vector<Item> items(b);
+    const Medium med = P->medium_for(b);
     for (int i = 0; i < b; ++i) {
-      items[i].m = P->med;
+      items[i].m = med;
       items[i].w = P->works[i];
     }
     std::unique_ptr<Exec> E(new Exec());
@@ -1045,15 +1105,13 @@ qpat_status set_tiles(qpat_plan P, int rt, int ct, int rthr, int cthr) {
   if (!col_tile_ok(P->prm.nx / 2, P->prm.ny, ct, cthr))
     return fail(QPAT_E_INVALID, "column tile: columns must be a power of two dividing nx/2, threads "
                                 "64/128/256/512, columns*ny <= 4*threads, within the LDS limit");
-  if (rt != P->rt || ct != P->ct || rthr != P->rthr || cthr != P->cthr) {
-    P->rt = P->med.rt = rt;
-    P->ct = P->med.ct = ct;
-    P->med.lrt = ilog2(rt);
-    P->med.lct = ilog2(ct);
-    P->med.srt = storage_rows(P->prm.ny, rt);
-    P->med.lsrt = ilog2(P->med.srt);
-    P->rthr = P->med.rthr = rthr;
-    P->cthr = P->med.cthr = cthr;
+  if (P->auto_shape || rt != P->rt || ct != P->ct || rthr != P->rthr || cthr != P->cthr) {
+    P->auto_shape = false;
+    P->rt = rt;
+    P->ct = ct;
+    P->rthr = rthr;
+    P->cthr = cthr;
+    shape_medium(P->med, rt, ct, rthr, cthr);
     HIPCHK(hipDeviceSynchronize());
     P->clear_execs();
   }
@@ -1365,8 +1423,9 @@ qpat_status grad_execs(qpat_plan P, int b, Exec** ef, Exec** ea) {
   auto it = P->grad_execs.find(b);
   if (it == P->grad_execs.end()) {
     std::vector<Item> fi(b), ai(b);
+    const Medium med = P->medium_for(b);
     for (int i = 0; i < b; ++i) {
-      fi[i].m = ai[i].m = P->med;
+      fi[i].m = ai[i].m = med;
       fi[i].w = P->works[i];
       ai[i].w = P->works[b + i];
     }
@@ -1479,6 +1538,7 @@ qpat_status qpat_tune(qpat_plan P, int32_t batch, qpat_stream stream) {
   hipStream_t st = (hipStream_t)stream;
   const int steps = 16;
   int brt = P->rt, bct = P->ct, brh = P->rthr, bch = P->cthr;
+  if (P->auto_shape) auto_tiles(nx, ny, batch, &brt, &bct, &brh, &bch);
   struct Cand {
     float ms;
     int rt, ct, rh, ch;
@@ -1652,7 +1712,7 @@ static qpat_status batch_build(qpat_batch B) {
     g->members = mem;
     std::vector<Item> items(mem.size());
     for (size_t k = 0; k < mem.size(); ++k) {
-      items[k].m = B->plans[mem[k]]->med;
+      items[k].m = B->plans[mem[k]]->medium_for(0);
       items[k].w = B->works[mem[k]];
     }
     STCHK(exec_build(g->exec, items));

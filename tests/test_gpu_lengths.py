@@ -94,3 +94,19 @@ def test_launch_over_several_lengths_bitwise(q):
         bat.set_schedule(schedule)
         for ref, g in zip(refs, bat.jtjv(xs)):
             assert np.array_equal(N(g), ref)
+
+
+@pytest.mark.parametrize("nx,ny,b", [(64, 64, 40), (1024, 64, 9), (64, 1024, 9), (192, 256, 24), (12, 8, 3), (512, 512, 3)])
+def test_shape_chosen_per_batch_size_is_bitwise(q, nx, ny, b):
+    """Until a shape is set, a launch takes one chosen from its vector count."""
+    prm, c0, rho0, _ = problem(nx, ny, 10, 0.75, ns=5)
+    prm["pml_size"] = 3
+    plan = q.Plan(prm, c0, rho0)
+    x = T(qi.gaussian_field((b, ny, nx), 6))
+    many = N(plan.jtjv(x))
+    for i in (0, b - 1):
+        assert np.array_equal(N(plan.jtjv(x[i])), many[i])
+    one = plan.tiles()
+    plan.set_tiles(*one)               # fixed from here on, the same shape for every count
+    assert plan.tiles() == one
+    assert np.array_equal(N(plan.jtjv(x)), many)
