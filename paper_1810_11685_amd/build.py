@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqpat.so")
 LENGTHS = (1024, 768, 512, 384, 256, 192, 128, 96, 64, 48, 32)   # line lengths with kernels of their own
-SOURCES = [*(f"passes{n}.hip" for n in LENGTHS), "kernels.hip", "plan.cpp", "recon.hip", "recon.cpp", "k3d.hip", "plan3d.cpp", "optical.hip", "optical.cpp", "probe.hip"]
+SOURCES = [*(f"passes{n}.hip" for n in LENGTHS), "kernels.hip", "plan.cpp", "recon.hip", "recon.cpp", "k3d.hip", "k3d_dense.hip", "plan3d.cpp", "optical.hip", "optical.cpp", "probe.hip"]
 
 # -packed-fp32-ops keeps the compiler from emitting packed FP32 VALU ops.
 HIP_FLAGS = ["-O3", "--offload-arch=gfx950", "-mcode-object-version=5", "-fPIC", "-std=c++17",

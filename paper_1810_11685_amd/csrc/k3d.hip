@@ -10,21 +10,9 @@
 // axis: radices 2, 3, 4, 5, 7, 8 as butterflies, any other prime factor as a
 // direct DFT stage, so axis lengths such as 33, 37, 49 and 53 of the paper's
 // 3-D grids (with their PML) run without padding.
-#include "k3d_internal.hpp"
+#include "k3d_device.hpp"
 
 namespace qpat3 {
-
-__device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
-__device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
-__device__ __forceinline__ float2 cmul(float2 a, float2 b) {
-  return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-__device__ __forceinline__ float2 cscale(float2 a, float s) { return make_float2(a.x * s, a.y * s); }
-
-// floor(a / d) for 0 <= a < 2^21, d >= 1, from rd = 1/d: (a + 1/2) / d lies at
-// least 1/(2d) from an integer and the float product errs by less than that.
-__device__ __forceinline__ int udiv(int a, float rd) { return int((float(a) + 0.5f) * rd); }
-__device__ __forceinline__ float rcp(int d) { return 1.0f / float(d); }
 
 // ---------------------------------------------------------------- small DFTs
 // cos and sin of 2 pi m / R for the odd radices (folded at compile time).
@@ -257,48 +245,6 @@ __device__ __forceinline__ void stage_ct(const float2* __restrict__ src, float2*
   }
 }
 
-// stage_generic for a prime length N transformed in one stage (no input
-// twiddles, one butterfly per line) with N a compile-time constant: the pair
-// loop unrolls and the work split folds.  Same operations in the same order.
-template <bool INV, int N>
-__device__ __forceinline__ void stage_prime_ct(const float2* __restrict__ src, float2* __restrict__ dst,
-                                               const LineMap m, const float2* __restrict__ tw) {
-  constexpr int H = (N - 1) / 2, PER = H + 1;
-  constexpr float RPER = 1.0f / float(PER);
-  const int total = m.nlines * PER;
-  const unsigned es = unsigned(m.es);
-  const float rlpg = rcp(m.lpg);
-  for (int t = threadIdx.x; t < total; t += blockDim.x) {
-    const int L = udiv(t, RPER), q = t - L * PER;
-    const unsigned off = line_off(m, unsigned(L), rlpg);
-    const float2* s = src + off;
-    float2 A = s[0], S = make_float2(0.f, 0.f);
-    if (q == 0) {
-#pragma unroll
-      for (int r = 1; r <= H; ++r) A = cadd(A, cadd(s[unsigned(r) * es], s[unsigned(N - r) * es]));
-      dst[off] = A;
-    } else {
-      int p = 0;   // (r q) mod N
-#pragma unroll
-      for (int r = 1; r <= H; ++r) {
-        const float2 xr = s[unsigned(r) * es], xm = s[unsigned(N - r) * es];
-        const float2 a = cadd(xr, xm), b = csub(xr, xm);
-        p += q;
-        if (p >= N) p -= N;
-        const float2 w = tw[p];   // cos(2 pi p / N) - i sin(2 pi p / N)
-        const float c = w.x, sn = -w.y;
-        A.x += c * a.x;
-        A.y += c * a.y;
-        S.x += sn * b.x;
-        S.y += sn * b.y;
-      }
-      const float2 iS = make_float2(-S.y, S.x);
-      dst[off + __umul24(unsigned(q), es)] = INV ? cadd(A, iS) : csub(A, iS);
-      dst[off + __umul24(unsigned(N - q), es)] = INV ? csub(A, iS) : cadd(A, iS);
-    }
-  }
-}
-
 // The runtime plan of an axis: every stage through stage_small or
 // stage_generic (barrier after each); returns the buffer holding the result.
 template <bool INV>
@@ -333,89 +279,30 @@ __device__ __forceinline__ float2* fft_axis_rt(float2* a, float2* b, const LineM
 
 // All stages of one axis (barrier after each); returns the buffer holding the
 // result (a or b).  AX is the axis length of a kernel instance whose every
-// transformed axis has that length (49 or 53: compile-time stages only, no
-// runtime plan in the instance); AX = 0 runs the runtime plan.  The launchers
-// pick AX from the plan's axis lengths.
+// transformed axis has that length (49 = 7 x 7 and 64 = 8 x 8: compile-time
+// stages only, no runtime plan in the instance); AX = 0 runs the runtime plan.
+// The launchers pick AX from the plan's axis lengths.
 template <bool INV, int AX>
 __device__ __forceinline__ float2* fft_axis(float2* a, float2* b, const LineMap m, const AxisPlan P,
                                             const float2* tw) {
-  if constexpr (AX == 49) {
-    // 7 x 7: the axes of the paper's 33^3-node grid with its 8-cell PML
-    stage_ct<7, INV, 49, 1>(a, b, m, tw);
+  if constexpr (AX == 0) {
+    return fft_axis_rt<INV>(a, b, m, P, tw);
+  } else {
+    constexpr int R = AX == 49 ? 7 : 8;
+    static_assert(R * R == AX, "two equal stages");
+    stage_ct<R, INV, AX, 1>(a, b, m, tw);
     __syncthreads();
-    stage_ct<7, INV, 49, 7>(b, a, m, tw);
+    stage_ct<R, INV, AX, R>(b, a, m, tw);
     __syncthreads();
     return a;
-  } else if constexpr (AX == 53) {
-    // prime: the axes of the paper's 37^3-node grid with its 8-cell PML
-    stage_prime_ct<INV, 53>(a, b, m, tw);
-    __syncthreads();
-    return b;
-  } else {
-    return fft_axis_rt<INV>(a, b, m, P, tw);
   }
-}
-
-// ---------------------------------------------------------------- block -> (item, tile)
-// Consecutive tiles of one item go to one XCD (work-groups are dispatched to
-// the XCDs round-robin).
-__device__ __forceinline__ bool locate(int nitems, int ntile, int chunk, int& item, int& tile) {
-  const int b = blockIdx.x;
-  const int i = (b & (kXcds - 1)) * chunk + (b / kXcds);
-  if (i >= nitems * ntile) return false;
-  item = i / ntile;
-  tile = i - item * ntile;
-  return true;
-}
-
-__device__ __forceinline__ Work3 shift(const Work3& w, long long off) {
-  Work3 r;
-  r.f = reinterpret_cast<float*>(reinterpret_cast<char*>(w.f) + off);
-  r.s = reinterpret_cast<float2*>(reinterpret_cast<char*>(w.s) + off);
-  r.part = reinterpret_cast<float*>(reinterpret_cast<char*>(w.part) + off);
-  return r;
-}
-
-__device__ __forceinline__ size_t spec_index(const Medium3& M, int f, int c, int l) {
-  return size_t(f) * M.ctiles * M.ct * M.nlines + size_t(c / M.ct) * (M.nlines * M.ct) + size_t(l) * M.ct +
-         (c % M.ct);
 }
 
 // ---------------------------------------------------------------- row pass
-template <int MODE>
-__device__ __forceinline__ void row_counts(const Medium3& M, int n, int& nin, int& nout) {
-  const bool first = (n == M.nt - 2);
-  switch (MODE) {
-    case R3_F1: nin = 3; nout = 3; break;
-    case R3_F2: nin = n == -1 ? 0 : 3; nout = 2; break;
-    case R3_F2L: nin = n == -1 ? 0 : 3; nout = 1; break;
-    case R3_F3: nin = 2; nout = 1; break;
-    case R3_A1: nin = first ? 0 : 1; nout = 2; break;
-    case R3_A1L: nin = first ? 0 : 1; nout = n == -1 ? 0 : 3; break;
-    case R3_A2: nin = 2; nout = n == -1 ? 0 : 3; break;
-    case R3_A3: nin = 3; nout = 3; break;
-    case R3_FWD1: nin = 0; nout = 1; break;
-    default: nin = 1; nout = 0; break;  // R3_INV1
-  }
-}
-
 // value of line j2 (of the tile) of field f in a buffer of paired lines
 __device__ __forceinline__ float& pc(float2* buf, int hp, int nx, int f, int j2, int x) {
   float2& z = buf[(f * hp + (j2 >> 1)) * nx + x];
   return (j2 & 1) ? z.y : z.x;
-}
-
-// The scalar cache is cold when a kernel starts, so every kernel-argument
-// load is a memory round trip, and the compiler issues each where its value is
-// first needed: behind the prologue's early-exit branch and the twiddle
-// staging loops.  These empty asm statements take the fields the prologue and
-// the load phase read (and the block size, an implicit argument) as SGPR
-// operands, so their loads issue as one batch at the top of the kernel.
-__device__ __forceinline__ void args3_batch(const Launch3& L, int ntile, int chunk, int n) {
-  const Medium3& m = L.m;
-  asm volatile("" ::"s"(ntile), "s"(chunk), "s"(n), "s"(blockDim.x), "s"(L.nitems), "s"(L.wstride), "s"(L.io),
-               "s"(L.w0.f), "s"(L.w0.s), "s"(L.w0.part), "s"(m.nx), "s"(m.ny), "s"(m.nz), "s"(m.nxh1),
-               "s"(m.nlines), "s"(m.nt), "s"(m.rt), "s"(m.ct), "s"(m.ctiles));
 }
 
 template <int MODE, int AX>
@@ -633,17 +520,6 @@ __device__ __forceinline__ float2 symbol(const Medium3& M, int code, int col, in
   }
 }
 
-template <int MODE>
-__device__ __forceinline__ int plane_code(int f, int code) {
-  switch (MODE) {
-    case P3_GRADP1:
-    case P3_GRADP2: return f == 0 ? OP_DXP : f == 1 ? OP_DYP : OP_DZP;
-    case P3_GRADM2: return f == 0 ? OP_DXM : f == 1 ? OP_DYM : OP_DZM;
-    case P3_FRAC: return f == 0 ? OP_LDIS : OP_LABS;
-    default: return code;
-  }
-}
-
 template <int MODE, int AX>
 __global__ void __launch_bounds__(kPlaneMax) plane3_kernel(const Launch3 L, int ntile, int chunk, int code, int n) {
   args3_batch(L, ntile, chunk, n);
@@ -725,17 +601,16 @@ __global__ void combine3_kernel(const Launch3 L) {
 template <int MODE>
 static hipError_t row_t(const Launch3& L, int ntile, int chunk, int n, size_t lds, hipStream_t st) {
   const dim3 g(chunk * kXcds), t(L.m.rthr);
-  // an instance with compile-time stages only for its own x length
-  if (L.m.px.n == 49)
-    hipLaunchKernelGGL((row3_kernel<MODE, 49>), g, t, lds, st, L, ntile, chunk, n);
-  else if (L.m.px.n == 53)
-    hipLaunchKernelGGL((row3_kernel<MODE, 53>), g, t, lds, st, L, ntile, chunk, n);
+  // (49-point lines take the dense row pass)
+  if (L.m.px.n == 64)
+    hipLaunchKernelGGL((row3_kernel<MODE, 64>), g, t, lds, st, L, ntile, chunk, n);
   else
     hipLaunchKernelGGL((row3_kernel<MODE, 0>), g, t, lds, st, L, ntile, chunk, n);
   return hipGetLastError();
 }
 
 hipError_t launch_row3(int mode, const Launch3& L, int ntile, int chunk, int n, hipStream_t st) {
+  if (dense3(L.m.nx)) return launch_row3_dense(mode, L, ntile, chunk, n, st);
   const size_t lds = row3_lds(L.m.nx, L.m.rt);
   switch (mode) {
     case R3_F1: return row_t<R3_F1>(L, ntile, chunk, n, lds, st);
@@ -758,14 +633,15 @@ static hipError_t plane_t(const Launch3& L, int ntile, int chunk, int code, int 
   // an instance with compile-time stages only when both transformed axes have its length
   if (L.m.py.n == 49 && L.m.pz.n == 49)
     hipLaunchKernelGGL((plane3_kernel<MODE, 49>), g, t, lds, st, L, ntile, chunk, code, n);
-  else if (L.m.py.n == 53 && L.m.pz.n == 53)
-    hipLaunchKernelGGL((plane3_kernel<MODE, 53>), g, t, lds, st, L, ntile, chunk, code, n);
+  else if (L.m.py.n == 64 && L.m.pz.n == 64)
+    hipLaunchKernelGGL((plane3_kernel<MODE, 64>), g, t, lds, st, L, ntile, chunk, code, n);
   else
     hipLaunchKernelGGL((plane3_kernel<MODE, 0>), g, t, lds, st, L, ntile, chunk, code, n);
   return hipGetLastError();
 }
 
 hipError_t launch_plane3(int mode, int code, const Launch3& L, int ntile, int chunk, int n, hipStream_t st) {
+  if (dense3_plane(L.m.ny, L.m.nz)) return launch_plane3_dense(mode, code, L, ntile, chunk, n, st);
   const size_t lds = plane3_lds(L.m.ny, L.m.nz, L.m.ct);
   switch (mode) {
     case P3_GRADP1: return plane_t<P3_GRADP1>(L, ntile, chunk, code, n, lds, st);
@@ -793,16 +669,14 @@ static hipError_t allow(K* k, size_t bytes) {
 
 template <int MODE>
 static hipError_t allow_row(size_t bytes) {
-  hipError_t e = allow(&row3_kernel<MODE, 0>, bytes);
-  if (e == hipSuccess) e = allow(&row3_kernel<MODE, 49>, bytes);
-  if (e == hipSuccess) e = allow(&row3_kernel<MODE, 53>, bytes);
-  return e;
+  const hipError_t e = allow(&row3_kernel<MODE, 0>, bytes);
+  return e != hipSuccess ? e : allow(&row3_kernel<MODE, 64>, bytes);
 }
 template <int MODE>
 static hipError_t allow_plane(size_t bytes) {
   hipError_t e = allow(&plane3_kernel<MODE, 0>, bytes);
   if (e == hipSuccess) e = allow(&plane3_kernel<MODE, 49>, bytes);
-  if (e == hipSuccess) e = allow(&plane3_kernel<MODE, 53>, bytes);
+  if (e == hipSuccess) e = allow(&plane3_kernel<MODE, 64>, bytes);
   return e;
 }
 

@@ -62,6 +62,7 @@ struct Medium3 {
   const float2 *dxp, *dxm, *dyp, *dym, *dzp, *dzm;  // 1-D symbols i k e^{+-i k d/2}: [nxh1] / [ny] / [nz]
   const float *kap, *ldis, *labs;              // [nxh1][nz][ny] (a column's lines contiguous), each / N
   const float2 *twx, *twy, *twz;               // e^{-2 pi i m / n}, m < n
+  const float *dfx, *dfxi, *dfy, *dfz, *dfzc;         // DFT matrices of axes up to kDenseMax, see dense3
   const int* tap_off;                          // [nlines + 1]
   const Tap3* taps;
   const int* node_off;                         // [nlines + 1] into nodes
@@ -117,6 +118,38 @@ enum OpCode3 : int { OP_DXP = 0, OP_DXM, OP_DYP, OP_DYM, OP_DZP, OP_DZM, OP_LDIS
 // transforms one field).
 inline size_t row3_lds(int nx, int rt) { return (size_t(2) * 3 * (rt / 2) * nx + nx) * sizeof(float2); }
 inline size_t plane3_lds(int ny, int nz, int ct) { return (size_t(2) * ct * ny * nz + ny + nz) * sizeof(float2); }
+
+// ---- axes transformed as dense DFTs on the matrix cores (k3d_dense.hip)
+// A length in [kDenseMin, kDenseMax] takes the symmetric DFT as matrix
+// products: with e_r = x_r + x_{n-r} and o_r = x_r - x_{n-r} (1 <= r <= n/2),
+// output q is x_0 + sum_r cos(2 pi q r / n) e_r -+ i sum_r sin(2 pi q r / n) o_r
+// and output n - q takes the other sign; r = n/2 counts half (its mirror is
+// itself).
+constexpr int kDenseMin = 18, kDenseMax = 63;
+constexpr int kDenseTiles = 2;   // 16-row tiles of outputs q
+constexpr int kDenseSteps = 8;   // steps of four inputs r
+inline __host__ __device__ bool dense3(int n) { return n >= kDenseMin && n <= kDenseMax; }
+// Planes transformed so: both axes in that range, but not 49 x 49, which the
+// compile-time 7 x 7 stages do in less than the matrix products (16 vectors,
+// the divergence pass of the velocities: 27 against 31 us; one vector: 9.1
+// against 9.4; its x-lines are dense: 26.3 against 28.4 and 6.8 against 8.1).
+inline __host__ __device__ bool dense3_plane(int ny, int nz) {
+  return dense3(ny) && dense3(nz) && !(ny == 49 && nz == 49);
+}
+// length classes of the kernels and their steps of four inputs
+inline __host__ __device__ constexpr int dense3_class(int n) { return n <= 31 ? 0 : n <= 33 ? 1 : n <= 49 ? 2 : 3; }
+inline __host__ __device__ constexpr int dense3_steps(int cls) { return cls <= 1 ? 4 : cls == 2 ? 6 : 8; }
+// A matrix as the matrix instruction's first operand, [tile][step / 2][lane]
+// [step % 2][cos, sin]: lane l of step s holds row q = 16 tile + l % 16 and
+// input r = S (l / 16) + s + 1 (S steps: a lane's inputs are neighbours).  The
+// chained form takes its inputs from the
+// accumulators of a preceding product (register i of row tile t in step 4 t + i):
+// r = 16 t + 4 (l / 16) + i, from r = 0, which counts half too.  Size in floats:
+constexpr size_t kDenseTable = size_t(kDenseTiles) * kDenseSteps * 2 * 64;
+static_assert(4 * kDenseTiles == kDenseSteps, "the chained form has four steps a tile");
+
+hipError_t launch_row3_dense(int mode, const Launch3& L, int ntile, int chunk, int n, hipStream_t st);
+hipError_t launch_plane3_dense(int mode, int code, const Launch3& L, int ntile, int chunk, int n, hipStream_t st);
 
 hipError_t launch_row3(int mode, const Launch3& L, int ntile, int chunk, int n, hipStream_t st);
 // blocks per column tile of a plane pass: one per field of the diagonal

@@ -348,6 +348,32 @@ qpat_status plan3_build(qpat_plan3d P, const double* c0, const double* rho0) {
     return t;
   };
   const std::vector<float2> twx = twid(nx), twy = twid(ny), twz = twid(nz);
+  // DFT matrices of the dense axes (layout in k3d_internal.hpp).  Factors come
+  // from the first half turn, so that rows q and n - q hold the same cosines
+  // and opposite sines to the bit.  half: the weight of an input that is its
+  // own mirror; other: of the rest (2 and 1 reversed for the inverse x
+  // transform, whose inputs are a half spectrum).
+  auto dft = [](int n, bool chained, double other, double half) {
+    std::vector<float> t(kDenseTable, 0.f);
+    const int S = dense3_steps(dense3_class(n));
+    for (int tile = 0; tile < kDenseTiles; ++tile)
+      for (int s = 0; s < kDenseSteps; ++s)
+        for (int l = 0; l < 64; ++l) {
+          const int q = 16 * tile + l % 16;
+          const int r = chained ? 16 * (s / 4) + 4 * (l / 16) + s % 4 : S * (l / 16) + s + 1;
+          if (2 * r > n || (!chained && s >= S)) continue;
+          const int m = q * r % n, mm = std::min(m, n - m);
+          const double w = (r == 0 || 2 * r == n) ? half : other, a = 2.0 * M_PI * double(mm) / double(n);
+          const double sn = (mm == 0 || 2 * mm == n) ? 0.0 : std::sin(a);
+          float* o = t.data() + ((size_t(tile) * (kDenseSteps / 2) + s / 2) * 64 + l) * 4 + 2 * (s % 2);
+          o[0] = float(w * std::cos(a));
+          o[1] = float(m == mm ? w * sn : -(w * sn));
+        }
+    return t;
+  };
+  const std::vector<float> dfx = dft(nx, false, 1.0, 0.5), dfxi = dft(nx, false, 2.0, 1.0),
+                           dfy = dft(ny, false, 1.0, 0.5), dfz = dft(nz, false, 1.0, 0.5),
+                           dfzc = dft(nz, true, 1.0, 0.5);
   std::vector<Tap3> taps;
   std::vector<int> toff;
   build_taps3(p, taps, toff);
@@ -373,6 +399,9 @@ qpat_status plan3_build(qpat_plan3d P, const double* c0, const double* rho0) {
                o_dym = cv.take<float2>(ny), o_dzp = cv.take<float2>(nz), o_dzm = cv.take<float2>(nz);
   const size_t o_kap = cv.take<float>(nk), o_ldis = cv.take<float>(nk), o_labs = cv.take<float>(nk);
   const size_t o_twx = cv.take<float2>(nx), o_twy = cv.take<float2>(ny), o_twz = cv.take<float2>(nz);
+  const size_t o_dfx = cv.take<float>(kDenseTable), o_dfxi = cv.take<float>(kDenseTable),
+               o_dfy = cv.take<float>(kDenseTable),
+               o_dfz = cv.take<float>(kDenseTable), o_dfzc = cv.take<float>(kDenseTable);
   const size_t o_toff = cv.take<int>(toff.size()), o_taps = cv.take<Tap3>(taps.size());
   const size_t o_noff = cv.take<int>(noff.size()), o_nodes = cv.take<ScatterNode>(nodes.size()),
                o_ent = cv.take<ScatterEntry>(entries.size());
@@ -403,6 +432,11 @@ qpat_status plan3_build(qpat_plan3d P, const double* c0, const double* rho0) {
   put(o_twx, twx.data(), nx * 8);
   put(o_twy, twy.data(), ny * 8);
   put(o_twz, twz.data(), nz * 8);
+  put(o_dfx, dfx.data(), kDenseTable * 4);
+  put(o_dfxi, dfxi.data(), kDenseTable * 4);
+  put(o_dfy, dfy.data(), kDenseTable * 4);
+  put(o_dfz, dfz.data(), kDenseTable * 4);
+  put(o_dfzc, dfzc.data(), kDenseTable * 4);
   put(o_toff, toff.data(), toff.size() * 4);
   put(o_taps, taps.data(), taps.size() * sizeof(Tap3));
   put(o_noff, noff.data(), noff.size() * 4);
@@ -451,6 +485,11 @@ qpat_status plan3_build(qpat_plan3d P, const double* c0, const double* rho0) {
   M.twx = (const float2*)(d + o_twx);
   M.twy = (const float2*)(d + o_twy);
   M.twz = (const float2*)(d + o_twz);
+  M.dfx = (const float*)(d + o_dfx);
+  M.dfxi = (const float*)(d + o_dfxi);
+  M.dfy = (const float*)(d + o_dfy);
+  M.dfz = (const float*)(d + o_dfz);
+  M.dfzc = (const float*)(d + o_dfzc);
   M.tap_off = (const int*)(d + o_toff);
   M.taps = (const Tap3*)(d + o_taps);
   M.node_off = (const int*)(d + o_noff);
@@ -513,13 +552,28 @@ void auto_shape3(const Medium3& base, int b, Medium3& m) {
   m.pthr = size_t(3) * b * base.ctiles <= size_t(kCus) ? 1024 : 512;
 }
 
+// Axes transformed as matrix products have their own: one tile of the matrix
+// instruction (16 lines) a row block, four waves (one per SIMD) a block.  The
+// shape that qpat3d_get_tiles names on automatic shape is the one above, which
+// these launches replace.
+void dense_shape3(const Medium3& base, Medium3& m) {
+  if (dense3(base.nx)) {
+    m.rt = 16;
+    m.rthr = 256;
+  }
+  if (dense3_plane(base.ny, base.nz)) m.pthr = 256;
+}
+
 qpat_status exec3(qpat_plan3d P, int b, Exec3** out) {
   S3CHK(reserve3(P, b));
   auto it = P->execs.find(b);
   if (it == P->execs.end()) {
     std::unique_ptr<Exec3> E(new Exec3());
     E->L.m = P->med;
-    if (P->auto_shape) auto_shape3(P->med, b, E->L.m);
+    if (P->auto_shape) {
+      auto_shape3(P->med, b, E->L.m);
+      dense_shape3(P->med, E->L.m);
+    }
     E->L.w0 = P->w0;
     E->L.wstride = (long long)P->item_bytes;
     E->L.nitems = b;
