@@ -37,9 +37,9 @@ struct qpat_optical_s {
   int cap = 0;
   void* mem = nullptr;
   OptCg c{};
-  std::vector<OptLevel> lv;   // multigrid levels, finest first
+  OptLevels lv;   // multigrid levels, finest first
   bool solved = false;
-  std::vector<double> h_rr, h_bb;
+  std::vector<double> h_rr;   // [0, cap): r.r, from cap: r.r of the right-hand side
   // hipGraph of one chunk of kCheckEvery CG iterations (chunks start at an
   // even iteration, so every full chunk launches the same kernels) for the
   // batch and tolerance it was captured with; the buffers never move
@@ -75,7 +75,7 @@ bool opt_ok(double tol, int max_iter) { return std::isfinite(tol) && tol > 0.0 &
 hipError_t cg_chunk(qpat_optical o, const OptCg& c, double tol2, hipStream_t st) {
   if (st == nullptr) {
     for (int k = 0; k < kCheckEvery; ++k) {
-      const hipError_t e = opt_launch_cg_iteration(c, o->lv.data(), int(o->lv.size()), k & 1, tol2, st);
+      const hipError_t e = opt_launch_cg_iteration(c, o->lv, k & 1, tol2, st);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -86,7 +86,7 @@ hipError_t cg_chunk(qpat_optical o, const OptCg& c, double tol2, hipStream_t st)
     if (e != hipSuccess) return e;
     hipError_t el = hipSuccess;
     for (int k = 0; k < kCheckEvery && el == hipSuccess; ++k)
-      el = opt_launch_cg_iteration(c, o->lv.data(), int(o->lv.size()), k & 1, tol2, st);
+      el = opt_launch_cg_iteration(c, o->lv, k & 1, tol2, st);
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(st, &g);
     if (el != hipSuccess || e != hipSuccess) {
@@ -105,13 +105,13 @@ hipError_t cg_chunk(qpat_optical o, const OptCg& c, double tol2, hipStream_t st)
   return hipGraphLaunch(o->graph_exec, st);
 }
 
-// Solve A x = rhs (already in c.rhs) for `batch` problems.
+// Solve A x = rhs (already in c.v.r[1]) for `batch` problems.
 qpat_status solve(qpat_optical o, int batch, double tol, int max_iter, int* iters, hipStream_t st) {
   OptCg c = o->c;
-  c.batch = batch;
+  c.batch = c.v.batch = batch;
   const double tol2 = tol * tol;
-  OPCHK(opt_launch_mg_setup(c, o->lv.data(), int(o->lv.size()), st));
-  OPCHK(opt_launch_cg_start(c, o->lv.data(), int(o->lv.size()), st));
+  OPCHK(opt_launch_mg_setup(c, o->lv, st));
+  OPCHK(opt_launch_cg_start(c, o->lv, st));
   int it = 0;
   while (it < max_iter) {
     const int chunk = std::min(kCheckEvery, max_iter - it);
@@ -120,23 +120,21 @@ qpat_status solve(qpat_optical o, int batch, double tol, int max_iter, int* iter
       it += chunk;
     } else {
       for (int k = 0; k < chunk; ++k, ++it)
-        OPCHK(opt_launch_cg_iteration(c, o->lv.data(), int(o->lv.size()), it & 1, tol2, st));
+        OPCHK(opt_launch_cg_iteration(c, o->lv, it & 1, tol2, st));
     }
-    OPCHK(hipMemcpyAsync(o->h_rr.data(), c.rr_next, sizeof(double) * batch, hipMemcpyDeviceToHost, st));
-    OPCHK(hipMemcpyAsync(o->h_bb.data(), c.bb, sizeof(double) * batch, hipMemcpyDeviceToHost, st));
+    OPCHK(hipMemcpyAsync(o->h_rr.data(), c.v.rr, sizeof(double) * (o->cap + batch), hipMemcpyDeviceToHost, st));
     OPCHK(hipStreamSynchronize(st));
     bool done = true;
-    for (int b = 0; b < batch; ++b) done = done && !(o->h_rr[b] > tol2 * o->h_bb[b]);
+    for (int b = 0; b < batch; ++b) done = done && !(o->h_rr[b] > tol2 * o->h_rr[o->cap + b]);
     if (done) break;
   }
-  OPCHK(opt_launch_cg_finish(c, st));
   if (iters) *iters = it;
   return QPAT_OK;
 }
 
 OptCg with_batch(qpat_optical o, int batch) {
   OptCg c = o->c;
-  c.batch = batch;
+  c.batch = c.v.batch = batch;
   return c;
 }
 
@@ -160,18 +158,13 @@ qpat_status qpat_optical_create(int32_t nx, int32_t ny, double dx, int32_t batch
   c.batch = batch;
   c.h = dx;
   c.nblk = std::min(kOptBlocks, (c.nn + kOptThreads - 1) / kOptThreads);
-  const size_t nn = size_t(c.nn) * batch, ne = size_t(c.ne) * batch, np = size_t(kOptBlocks) * batch;
+  const size_t nn = size_t(c.nn) * batch, ne = size_t(c.ne) * batch, np = size_t(cgmg::kParts) * batch;
   // multigrid levels on the node grid: 2 x 2 aggregates down to a single node
-  std::vector<std::pair<int, int>> dims{{nx + 1, ny + 1}};
-  while (int64_t(dims.back().first) * dims.back().second > 1)
-    dims.push_back({(dims.back().first + 1) / 2, (dims.back().second + 1) / 2});
-  if (int(dims.size()) > kOptMgMaxLevels) {
+  if (!o->lv.plan(nx + 1, ny + 1)) {
     delete o;
     return set_error(QPAT_E_UNSUPPORTED, "mesh needs too many multigrid levels");
   }
-  size_t coarse = 0;
-  for (size_t l = 1; l < dims.size(); ++l) coarse += size_t(dims[l].first) * dims[l].second * batch;
-  const size_t total = 4 * ne + 7 * nn + 3 * np + 5 * size_t(batch) + 4 * size_t(batch) + 6 * nn + 8 * coarse;
+  const size_t total = 4 * ne + 8 * nn + 3 * np + 4 * size_t(batch) + 4 * size_t(batch) + 5 * nn + o->lv.words(batch);
   void* mem = nullptr;
   hipError_t e = hipMalloc(&mem, total * sizeof(double));
   if (e != hipSuccess) {
@@ -179,6 +172,11 @@ qpat_status qpat_optical_create(int32_t nx, int32_t ny, double dx, int32_t batch
     return set_error(QPAT_E_OOM, "optical work space");
   }
   o->mem = mem;
+  e = opt_allow_lds();
+  if (e != hipSuccess) {
+    delete o;
+    return set_error(QPAT_E_HIP, std::string("optical set-up: ") + hipGetErrorString(e));
+  }
   double* p = static_cast<double*>(mem);
   auto take = [&](size_t n) {
     double* r = p;
@@ -190,42 +188,30 @@ qpat_status qpat_optical_create(int32_t nx, int32_t ny, double dx, int32_t batch
   c.ek = take(ne);
   c.em = take(ne);
   c.phi = take(nn);
-  c.rhs = take(nn);
-  c.x = take(nn);
-  c.r = take(nn);
-  c.p = take(nn);
-  c.q = take(nn);
-  c.dinv = take(nn);
-  c.part_rz = take(np);
-  c.part_rr = take(np);
-  c.part_pq = take(np);
-  c.rz = take(2 * size_t(batch));
-  c.rr = take(batch);
-  c.rr_next = take(batch);
-  c.bb = take(batch);
+  c.v.x = take(nn);
+  c.v.r[0] = take(nn);
+  c.v.r[1] = take(nn);
+  c.v.p[0] = take(nn);
+  c.v.p[1] = take(nn);
+  c.v.q = take(nn);
+  c.v.z = take(nn);
+  c.v.part_rz = take(np);
+  c.v.part_rr = take(np);
+  c.v.part_pq = take(np);
+  c.v.rz = take(2 * size_t(batch));
+  c.v.rr = take(batch);
+  c.v.bb = take(batch);
   c.cur = take(4 * size_t(batch));
-  c.z = take(nn);
-  {
-    // level 0 works on the CG vectors: b = r, result t = z
-    OptLevel L{nx + 1, ny + 1, take(nn), take(nn), take(nn), take(nn), c.dinv, c.r, take(nn), c.z};
-    o->lv.push_back(L);
-  }
-  for (size_t l = 1; l < dims.size(); ++l) {
-    const size_t m = size_t(dims[l].first) * dims[l].second * batch;
-    OptLevel L{dims[l].first, dims[l].second, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-    L.sc = take(m);
-    L.se = take(m);
-    L.sn = take(m);
-    L.sd = take(m);
-    L.dinv = take(m);
-    L.b = take(m);
-    L.x = take(m);
-    L.t = take(m);
-    o->lv.push_back(L);
-  }
+  OptLevel& L0 = o->lv.lv[0];
+  L0.sc = take(nn);
+  L0.se = take(nn);
+  L0.sn = take(nn);
+  L0.sd = take(nn);
+  L0.dinv = take(nn);
+  L0.b = c.v.r[0];   // at the start
+  o->lv.carve(batch, take);
   o->cap = batch;
-  o->h_rr.resize(batch);
-  o->h_bb.resize(batch);
+  o->h_rr.resize(2 * size_t(batch));
   *out = o;
   return QPAT_OK;
 }

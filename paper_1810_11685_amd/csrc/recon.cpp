@@ -41,10 +41,12 @@ constexpr int kCheckEvery = 8;  // CG iterations between host convergence checks
 struct qpat_tv_s {
   int nx = 0, ny = 0, cap = 0;
   void* mem = nullptr;
-  TvCg c{};
-  std::vector<MgLevel> lv;   // multigrid levels, finest first
+  cgmg::Vectors c{};
+  double *wh = nullptr, *wv = nullptr;   // edge weights C (horizontal / vertical edge of each node)
+  TvLevels lv;               // multigrid levels, finest first
   bool weights = false;
-  std::vector<double> h_rr, h_bb, h_part;
+  std::vector<double> h_rr;  // [0, cap): r.r, from cap: r.r of the right-hand side
+  std::vector<double> h_part;
   ~qpat_tv_s() {
     if (mem) (void)hipFree(mem);
   }
@@ -63,23 +65,24 @@ qpat_status qpat_tv_create(int32_t nx, int32_t ny, int32_t batch, qpat_tv* out) 
   t->ny = ny;
   t->cap = batch;
   const size_t n = size_t(nx) * ny * batch;
-  const size_t parts = size_t(batch) * kRedBlocks;
+  static_assert(kRedBlocks <= cgmg::kParts, "qpat_tv_value keeps its partials in part_pq");
+  const size_t parts = size_t(batch) * cgmg::kParts;
   // multigrid levels: 2 x 2 aggregates down to a single node
-  std::vector<std::pair<int, int>> dims{{nx, ny}};
-  while (int64_t(dims.back().first) * dims.back().second > 1)
-    dims.push_back({(dims.back().first + 1) / 2, (dims.back().second + 1) / 2});
-  if (int(dims.size()) > kMgMaxLevels) {
+  if (!t->lv.plan(nx, ny)) {
     delete t;
     return set_error(QPAT_E_UNSUPPORTED, "grid needs too many multigrid levels");
   }
-  size_t coarse = 0;
-  for (size_t l = 1; l < dims.size(); ++l) coarse += size_t(dims[l].first) * dims[l].second * batch;
-  const size_t words = 8 * n + 3 * parts + 2 * size_t(batch) + 3 * size_t(batch) + 2 * n + 7 * coarse;
+  const size_t words = 10 * n + 3 * parts + 4 * size_t(batch) + t->lv.words(batch);
   hipError_t e = hipMalloc(&t->mem, words * sizeof(double));
   if (e != hipSuccess) {
     delete t;
     return set_error(e == hipErrorOutOfMemory ? QPAT_E_OOM : QPAT_E_HIP,
                      std::string("qpat_tv_create: ") + hipGetErrorString(e));
+  }
+  e = tv_allow_lds();
+  if (e != hipSuccess) {
+    delete t;
+    return set_error(QPAT_E_HIP, std::string("qpat_tv_create: ") + hipGetErrorString(e));
   }
   double* d = static_cast<double*>(t->mem);
   auto take = [&](size_t cnt) {
@@ -88,37 +91,29 @@ qpat_status qpat_tv_create(int32_t nx, int32_t ny, int32_t batch, qpat_tv* out) 
     return p;
   };
   t->c.x = take(n);
-  t->c.r = take(n);
-  t->c.z = take(n);
-  t->c.p = take(n);
+  t->c.r[0] = take(n);
+  t->c.r[1] = take(n);
+  t->c.p[0] = take(n);
+  t->c.p[1] = take(n);
   t->c.q = take(n);
-  t->c.dinv = take(n);
-  t->c.wh = take(n);
-  t->c.wv = take(n);
+  t->c.z = take(n);
+  t->wh = take(n);
+  t->wv = take(n);
   t->c.part_rz = take(parts);
   t->c.part_rr = take(parts);
   t->c.part_pq = take(parts);
   t->c.rz = take(2 * size_t(batch));
   t->c.rr = take(batch);
-  t->c.rr_next = take(batch);
   t->c.bb = take(batch);
-  // level 0 works on the CG vectors: b = r, result t = z
-  t->lv.push_back(MgLevel{nx, ny, t->c.wh, t->c.wv, take(n), t->c.dinv, t->c.r, take(n), t->c.z});
-  for (size_t l = 1; l < dims.size(); ++l) {
-    const size_t m = size_t(dims[l].first) * dims[l].second * batch;
-    MgLevel L{dims[l].first, dims[l].second, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-    L.wh = take(m);
-    L.wv = take(m);
-    L.g = take(m);
-    L.dinv = take(m);
-    L.b = take(m);
-    L.x = take(m);
-    L.t = take(m);
-    t->lv.push_back(L);
-  }
-  t->h_rr.resize(batch);
-  t->h_bb.resize(batch);
-  t->h_part.resize(parts);
+  MgLevel& L0 = t->lv.lv[0];
+  L0.uniform = 1;
+  L0.wh = t->wh;
+  L0.wv = t->wv;
+  L0.dinv = take(n);
+  L0.b = t->c.r[0];   // at the start
+  t->lv.carve(batch, take);
+  t->h_rr.resize(2 * size_t(batch));
+  t->h_part.resize(size_t(batch) * kRedBlocks);
   *out = t;
   return QPAT_OK;
 }
@@ -140,7 +135,7 @@ qpat_status qpat_tv_set_weights(qpat_tv tv, const float* x, double beta, int32_t
   if (s != QPAT_OK) return s;
   if (!x) return set_error(QPAT_E_INVALID, "x is NULL");
   if (!(std::isfinite(beta) && beta > 0.0)) return set_error(QPAT_E_INVALID, "beta must be finite and > 0");
-  TVCHK(launch_tv_weights(x, tv->nx, tv->ny, batch, beta, tv->c.wh, tv->c.wv, (hipStream_t)stream));
+  TVCHK(launch_tv_weights(x, tv->nx, tv->ny, batch, beta, tv->wh, tv->wv, (hipStream_t)stream));
   tv->weights = true;
   return QPAT_OK;
 }
@@ -151,7 +146,7 @@ qpat_status qpat_tv_apply(qpat_tv tv, double gamma, const float* x, float* y, in
   if (!x || !y) return set_error(QPAT_E_INVALID, "NULL field");
   if (!tv->weights) return set_error(QPAT_E_INVALID, "qpat_tv_set_weights has not been called");
   if (!(std::isfinite(gamma) && gamma >= 0.0)) return set_error(QPAT_E_INVALID, "gamma must be finite and >= 0");
-  TVCHK(launch_tv_apply(x, y, tv->c.wh, tv->c.wv, tv->nx, tv->ny, batch, gamma, (hipStream_t)stream));
+  TVCHK(launch_tv_apply(x, y, tv->wh, tv->wv, tv->nx, tv->ny, batch, gamma, (hipStream_t)stream));
   return QPAT_OK;
 }
 
@@ -166,23 +161,23 @@ qpat_status qpat_tv_solve(qpat_tv tv, double gamma, const float* r, float* z, in
   if (max_iter < 1) return set_error(QPAT_E_INVALID, "max_iter must be >= 1");
   hipStream_t st = (hipStream_t)stream;
   const double tol2 = tol * tol;
-  const int nlev = int(tv->lv.size());
-  TVCHK(launch_mg_setup(tv->lv.data(), nlev, batch, gamma, st));
-  TVCHK(launch_cg_start(r, tv->c, tv->lv.data(), nlev, tv->nx, tv->ny, batch, st));
+  cgmg::Vectors c = tv->c;
+  c.batch = batch;
+  tv->lv.lv[0].gamma = gamma;
+  TVCHK(launch_mg_setup(tv->lv, batch, st));
+  TVCHK(launch_cg_start(r, c, tv->lv, st));
   int it = 0;
   while (it < max_iter) {
     const int chunk = std::min(kCheckEvery, max_iter - it);
     for (int k = 0; k < chunk; ++k, ++it)
-      TVCHK(launch_cg_iteration(tv->c, tv->lv.data(), nlev, tv->nx, tv->ny, batch, gamma, it & 1, tol2, st));
-    // the pending r.r of the last iteration is published by the next cg_q or by the finish
-    TVCHK(hipMemcpyAsync(tv->h_rr.data(), tv->c.rr_next, sizeof(double) * batch, hipMemcpyDeviceToHost, st));
-    TVCHK(hipMemcpyAsync(tv->h_bb.data(), tv->c.bb, sizeof(double) * batch, hipMemcpyDeviceToHost, st));
+      TVCHK(launch_cg_iteration(c, tv->lv, it & 1, tol2, st));
+    TVCHK(hipMemcpyAsync(tv->h_rr.data(), c.rr, sizeof(double) * (tv->cap + batch), hipMemcpyDeviceToHost, st));
     TVCHK(hipStreamSynchronize(st));
     bool done = true;
-    for (int b = 0; b < batch; ++b) done = done && !(tv->h_rr[b] > tol2 * tv->h_bb[b]);
+    for (int b = 0; b < batch; ++b) done = done && !(tv->h_rr[b] > tol2 * tv->h_rr[tv->cap + b]);
     if (done) break;
   }
-  TVCHK(launch_cg_finish(tv->c, z, tv->nx, tv->ny, batch, st));
+  TVCHK(launch_cg_finish(c, z, size_t(tv->nx) * tv->ny * batch, st));
   if (iters) *iters = it;
   return QPAT_OK;
 }

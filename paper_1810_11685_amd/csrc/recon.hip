@@ -7,7 +7,7 @@
 // beta)^(-1/2)); M_gamma = D^T C D + gamma I.  Edge weights are stored per
 // node: wh[j][i] for the edge (j, i)-(j, i+1), wv[j][i] for (j, i)-(j+1, i)
 // (zero past the last column / row).  M_gamma z = r is solved by conjugate
-// gradients in FP64, preconditioned by one multigrid V-cycle: 2 x 2
+// gradients in FP64 (cg_mg.hpp), preconditioned by one multigrid V-cycle: 2 x 2
 // aggregation with piecewise-constant prolongation P, whose Galerkin coarse
 // operators P^T A P keep the same five-point form (a coarse edge weighs the
 // sum of the fine edges between its two aggregates, the diagonal term sums
@@ -127,48 +127,14 @@ tv_value_kernel(const float* __restrict__ x, int nx, int ny, double beta, double
   if (threadIdx.x == 0) part[size_t(b) * kRedBlocks + blockIdx.x] = s;
 }
 
-// ---- multigrid V-cycle (levels as in MgLevel)
-// y = (A u)_k at node (j, i) of a level: diagonal term plus edge differences
-template <typename U>
-__device__ __forceinline__ double level_op(const MgLevel& L, size_t base, int k, int i, int j, U u) {
-  const double uc = u(k, i, j);
-  double y = L.g[base + k] * uc;
-  if (i + 1 < L.nx) y += L.wh[base + k] * (uc - u(k + 1, i + 1, j));
-  if (i > 0) y += L.wh[base + k - 1] * (uc - u(k - 1, i - 1, j));
-  if (j + 1 < L.ny) y += L.wv[base + k] * (uc - u(k + L.nx, i, j + 1));
-  if (j > 0) y += L.wv[base + k - L.nx] * (uc - u(k - L.nx, i, j - 1));
-  return y;
-}
-
-__global__ void __launch_bounds__(kRedThreads) mg_fill_kernel(double* __restrict__ a, size_t n, double v) {
-  for (size_t k = size_t(blockIdx.x) * blockDim.x + threadIdx.x; k < n; k += size_t(gridDim.x) * blockDim.x) a[k] = v;
-}
-
-// coarse level operator from the finer one (one thread per coarse node)
-__global__ void __launch_bounds__(kRedThreads) mg_coarsen_kernel(MgLevel f, MgLevel c) {
-  const int b = blockIdx.y, nc = c.nx * c.ny;
-  const size_t bf = size_t(b) * f.nx * f.ny, bc = size_t(b) * nc;
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < nc; k += gridDim.x * blockDim.x) {
-    const int J = k / c.nx, I = k - J * c.nx, j0 = 2 * J, i0 = 2 * I;
-    double g = 0.0, h = 0.0, v = 0.0;
-    for (int j = j0; j < j0 + 2 && j < f.ny; ++j) {
-      for (int i = i0; i < i0 + 2 && i < f.nx; ++i) g += f.g[bf + size_t(j) * f.nx + i];
-      if (I + 1 < c.nx) h += f.wh[bf + size_t(j) * f.nx + i0 + 1];   // edge (j, i0+1)-(j, i0+2)
-    }
-    if (J + 1 < c.ny)
-      for (int i = i0; i < i0 + 2 && i < f.nx; ++i) v += f.wv[bf + size_t(j0 + 1) * f.nx + i];
-    c.g[bc + k] = g;
-    c.wh[bc + k] = h;
-    c.wv[bc + k] = v;
-  }
-}
-
+// ---- solve of M_gamma z = r (cg_mg.hpp)
+// inverse diagonal of level 0
 __global__ void __launch_bounds__(kRedThreads) mg_diag_kernel(MgLevel L) {
   const int b = blockIdx.y, n = L.nx * L.ny;
   const size_t base = size_t(b) * n;
   for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) {
     const int j = k / L.nx, i = k - j * L.nx;
-    double d = L.g[base + k];
+    double d = L.gamma;
     if (i + 1 < L.nx) d += L.wh[base + k];
     if (i > 0) d += L.wh[base + k - 1];
     if (j + 1 < L.ny) d += L.wv[base + k];
@@ -177,166 +143,10 @@ __global__ void __launch_bounds__(kRedThreads) mg_diag_kernel(MgLevel L) {
   }
 }
 
-// first sweep from x = 0: x = om dinv b
-__global__ void __launch_bounds__(kRedThreads) mg_scale_kernel(MgLevel L, double om) {
-  const int b = blockIdx.y, n = L.nx * L.ny;
-  const size_t base = size_t(b) * n;
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x)
-    L.x[base + k] = om * L.dinv[base + k] * L.b[base + k];
-}
-
-// coarse right-hand side: the aggregate sums of the residual b - A x of the
-// first sweep from x = 0, x = om dinv b (recomputed where it is needed)
-__global__ void __launch_bounds__(kRedThreads) mg_restrict_kernel(MgLevel f, MgLevel c, double om) {
-  const int b = blockIdx.y, nc = c.nx * c.ny;
-  const size_t bf = size_t(b) * f.nx * f.ny, bc = size_t(b) * nc;
-  auto xf = [&](int kk, int, int) { return om * f.dinv[bf + kk] * f.b[bf + kk]; };
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < nc; k += gridDim.x * blockDim.x) {
-    const int J = k / c.nx, I = k - J * c.nx;
-    double acc = 0.0;
-    for (int j = 2 * J; j < 2 * J + 2 && j < f.ny; ++j)
-      for (int i = 2 * I; i < 2 * I + 2 && i < f.nx; ++i) {
-        const int kf = j * f.nx + i;
-        acc += f.b[bf + kf] - level_op(f, bf, kf, i, j, xf);
-      }
-    c.b[bc + k] = acc;
-  }
-}
-
-// coarse correction and post-smoothing: with x' = om dinv b + P xc (the
-// first sweep's x, recomputed), t = x' + om dinv (b - A x')
-__global__ void __launch_bounds__(kRedThreads) mg_post_kernel(MgLevel f, const double* __restrict__ xc, int nxc,
-                                                               int nyc, double om) {
-  const int b = blockIdx.y, n = f.nx * f.ny;
-  const size_t bf = size_t(b) * n, bc = size_t(b) * nxc * nyc;
-  auto xp = [&](int kk, int ii, int jj) {
-    return om * f.dinv[bf + kk] * f.b[bf + kk] + xc[bc + size_t(jj >> 1) * nxc + (ii >> 1)];
-  };
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) {
-    const int j = k / f.nx, i = k - j * f.nx;
-    const double y = level_op(f, bf, k, i, j, xp);
-    f.t[bf + k] = xp(k, i, j) + om * f.dinv[bf + k] * (f.b[bf + k] - y);
-  }
-}
-
-// ---- conjugate gradients for M_gamma z = r, per field (FP64)
-// start: x = 0, r = rhs; partials of r.r (z and r.z follow the V-cycle)
-__global__ void __launch_bounds__(kRedThreads)
-cg_start_kernel(const float* __restrict__ rhs, TvCg c, int nx, int ny) {
-  __shared__ double red[kRedThreads / 64];
-  const int b = blockIdx.y;
-  const size_t n = size_t(nx) * ny, base = size_t(b) * n;
-  double rr = 0.0;
-  for (size_t k = size_t(blockIdx.x) * blockDim.x + threadIdx.x; k < n; k += size_t(gridDim.x) * blockDim.x) {
-    const double r = rhs[base + k];
-    c.x[base + k] = 0.0;
-    c.r[base + k] = r;
-    rr += r * r;
-  }
-  const double s = block_sum(rr, red);
-  if (threadIdx.x == 0) c.part_rr[size_t(b) * kRedBlocks + blockIdx.x] = s;
-}
-
-// partials of r.z for the z the V-cycle left; at the start also p = z
-__global__ void __launch_bounds__(kRedThreads) cg_rz_kernel(TvCg c, int nx, int ny, int set_p) {
-  __shared__ double red[kRedThreads / 64];
-  const int b = blockIdx.y;
-  const size_t n = size_t(nx) * ny, base = size_t(b) * n;
-  double rz = 0.0;
-  for (size_t k = size_t(blockIdx.x) * blockDim.x + threadIdx.x; k < n; k += size_t(gridDim.x) * blockDim.x) {
-    const double z = c.z[base + k];
-    rz += c.r[base + k] * z;
-    if (set_p) c.p[base + k] = z;
-  }
-  const double s = block_sum(rz, red);
-  if (threadIdx.x == 0) c.part_rz[size_t(b) * kRedBlocks + blockIdx.x] = s;
-}
-
-// totals of the start partials: rz[0][b], rr[b], bb[b] = r.r of the right-hand side
-__global__ void __launch_bounds__(kRedThreads) cg_start_total_kernel(TvCg c) {
-  __shared__ double red[kRedThreads / 64];
-  const int b = blockIdx.x;
-  const double rz = partial_total(c.part_rz, b, red);
-  const double rr = partial_total(c.part_rr, b, red);
-  if (threadIdx.x == 0) {
-    c.rz[b] = rz;
-    c.rr[b] = rr;
-    c.rr_next[b] = rr;
-    c.bb[b] = rr;
-  }
-}
-
-// q = M_gamma p; partials of p.q.  Block (0, 0) also publishes the r.r of the
-// previous iteration (nothing reads rr while this kernel runs).
-__global__ void __launch_bounds__(kRedThreads) cg_q_kernel(TvCg c, int nx, int ny, double gamma) {
-  __shared__ double red[kRedThreads / 64];
-  const int b = blockIdx.y;
-  if (blockIdx.x == 0 && blockIdx.y == 0)
-    for (int t = threadIdx.x; t < int(gridDim.y); t += blockDim.x) c.rr[t] = c.rr_next[t];
-  const size_t n = size_t(nx) * ny, base = size_t(b) * n;
-  double pq = 0.0;
-  for (size_t k = size_t(blockIdx.x) * blockDim.x + threadIdx.x; k < n; k += size_t(gridDim.x) * blockDim.x) {
-    const int j = int(k / nx), i = int(k - size_t(j) * nx);
-    const double q = mgamma_at(c.p, c.wh, c.wv, base, k, i, j, nx, ny, gamma);
-    c.q[base + k] = q;
-    pq += c.p[base + k] * q;
-  }
-  const double s = block_sum(pq, red);
-  if (threadIdx.x == 0) c.part_pq[size_t(b) * kRedBlocks + blockIdx.x] = s;
-}
-
-// alpha = r.z / p.q (0 once the field has converged: r.r <= tol^2 b.b);
-// x += alpha p; r -= alpha q; partials of the new r.r.  rz[par] holds the
-// current r.z, the new one goes to rz[1 - par] (cg_dir).
-__global__ void __launch_bounds__(kRedThreads)
-cg_update_kernel(TvCg c, int nx, int ny, int par, double tol2) {
-  __shared__ double red[kRedThreads / 64];
-  const int b = blockIdx.y, nb = gridDim.y;
-  const size_t n = size_t(nx) * ny, base = size_t(b) * n;
-  const double pq = partial_total(c.part_pq, b, red);
-  const double rz = c.rz[size_t(par) * nb + b];
-  const bool live = c.rr[b] > tol2 * c.bb[b] && pq > 0.0;
-  const double alpha = live ? rz / pq : 0.0;
-  double rr = 0.0;
-  for (size_t k = size_t(blockIdx.x) * blockDim.x + threadIdx.x; k < n; k += size_t(gridDim.x) * blockDim.x) {
-    c.x[base + k] += alpha * c.p[base + k];
-    const double r = c.r[base + k] - alpha * c.q[base + k];
-    c.r[base + k] = r;
-    rr += r * r;
-  }
-  const double s2 = block_sum(rr, red);
-  if (threadIdx.x == 0) c.part_rr[size_t(b) * kRedBlocks + blockIdx.x] = s2;
-}
-
-// beta = r.z(new) / r.z(old); p = z + beta p; block 0 stores the new r.z and r.r.
-__global__ void __launch_bounds__(kRedThreads)
-cg_dir_kernel(TvCg c, int nx, int ny, int par, double tol2) {
-  __shared__ double red[kRedThreads / 64];
-  const int b = blockIdx.y, nb = gridDim.y;
-  const size_t n = size_t(nx) * ny, base = size_t(b) * n;
-  const double rzn = partial_total(c.part_rz, b, red);
-  const double rr = partial_total(c.part_rr, b, red);
-  const double rz = c.rz[size_t(par) * nb + b];
-  const bool live = c.rr[b] > tol2 * c.bb[b];
-  const double beta = (live && rz > 0.0) ? rzn / rz : 0.0;
+__global__ void __launch_bounds__(kRedThreads) cg_finish_kernel(const double* __restrict__ x, float* __restrict__ out,
+                                                                size_t n) {
   for (size_t k = size_t(blockIdx.x) * blockDim.x + threadIdx.x; k < n; k += size_t(gridDim.x) * blockDim.x)
-    c.p[base + k] = c.z[base + k] + beta * c.p[base + k];
-  // every block has read rz[par] and rr[b] above; the new values go to rz[1 - par]
-  // and to rr_next, which the next cg_q publishes as rr
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    c.rz[size_t(1 - par) * nb + b] = live ? rzn : rz;
-    c.rr_next[b] = live ? rr : c.rr[b];
-  }
-}
-
-__global__ void __launch_bounds__(kRedThreads)
-cg_finish_kernel(TvCg c, float* __restrict__ out, int nx, int ny) {
-  const int b = blockIdx.y;
-  if (blockIdx.x == 0 && blockIdx.y == 0)
-    for (int t = threadIdx.x; t < int(gridDim.y); t += blockDim.x) c.rr[t] = c.rr_next[t];
-  const size_t n = size_t(nx) * ny, base = size_t(b) * n;
-  for (size_t k = size_t(blockIdx.x) * blockDim.x + threadIdx.x; k < n; k += size_t(gridDim.x) * blockDim.x)
-    out[base + k] = float(c.x[base + k]);
+    out[k] = float(x[k]);
 }
 
 __global__ void __launch_bounds__(kRedThreads)
@@ -487,68 +297,28 @@ hipError_t launch_tv_value(const float* x, int nx, int ny, int batch, double bet
   return hipGetLastError();
 }
 
-namespace {
-
-// blocks per field for a level of n nodes (grid-stride loops cover the rest)
-dim3 level_grid(const MgLevel& L, int batch) {
-  const int n = L.nx * L.ny;
-  return dim3(unsigned(std::min(kRedBlocks, (n + kRedThreads - 1) / kRedThreads)), unsigned(batch));
+hipError_t launch_mg_setup(const TvLevels& L, int batch, hipStream_t st) {
+  const MgLevel& F = L.lv[0];
+  const int nb = std::min(cgmg::kSetupBlocks, (F.nx * F.ny + kRedThreads - 1) / kRedThreads);
+  hipLaunchKernelGGL(mg_diag_kernel, dim3(nb, batch), dim3(kRedThreads), 0, st, F);
+  return L.setup(batch, st);
 }
-
-// z = V-cycle applied to level 0's b; the result lands in level 0's t
-hipError_t launch_vcycle(const MgLevel* lv, int nlev, int batch, hipStream_t st) {
-  for (int l = 0; l + 1 < nlev; ++l)
-    hipLaunchKernelGGL(mg_restrict_kernel, level_grid(lv[l + 1], batch), dim3(kRedThreads), 0, st, lv[l], lv[l + 1],
-                       kMgOmega);
-  // coarsest level: one node per field, solved exactly (x = b / diag)
-  hipLaunchKernelGGL(mg_scale_kernel, level_grid(lv[nlev - 1], batch), dim3(kRedThreads), 0, st, lv[nlev - 1], 1.0);
-  for (int l = nlev - 2; l >= 0; --l) {
-    const double* xc = (l + 1 == nlev - 1) ? lv[l + 1].x : lv[l + 1].t;
-    hipLaunchKernelGGL(mg_post_kernel, level_grid(lv[l], batch), dim3(kRedThreads), 0, st, lv[l], xc, lv[l + 1].nx,
-                       lv[l + 1].ny, kMgOmega);
-  }
+hipError_t launch_cg_start(const float* rhs, const cgmg::Vectors& c, const TvLevels& L, hipStream_t st) {
+  const MgLevel& F = L.lv[0];
+  hipLaunchKernelGGL((cgmg::start_kernel<float>), dim3(cgmg::blocks(F.nx, F.ny), c.batch), dim3(cgmg::kThreads), 0, st, c,
+                     rhs, F.fs);
+  return L.start(c, st);
+}
+hipError_t launch_cg_iteration(const cgmg::Vectors& c, const TvLevels& L, int par, double tol2, hipStream_t st) {
+  return L.iteration(c, par, tol2, st);
+}
+// the solution in FP32; n values over all fields
+hipError_t launch_cg_finish(const cgmg::Vectors& c, float* out, size_t n, hipStream_t st) {
+  const size_t nb = std::min<size_t>(4096, (n + kRedThreads - 1) / kRedThreads);
+  hipLaunchKernelGGL(cg_finish_kernel, dim3(unsigned(nb)), dim3(kRedThreads), 0, st, c.x, out, n);
   return hipGetLastError();
 }
-
-}  // namespace
-
-hipError_t launch_mg_setup(const MgLevel* lv, int nlev, int batch, double gamma, hipStream_t st) {
-  const size_t n0 = size_t(lv[0].nx) * lv[0].ny * batch;
-  hipLaunchKernelGGL(mg_fill_kernel, dim3(unsigned(std::min<size_t>(4096, (n0 + kRedThreads - 1) / kRedThreads))),
-                     dim3(kRedThreads), 0, st, lv[0].g, n0, gamma);
-  for (int l = 0; l + 1 < nlev; ++l)
-    hipLaunchKernelGGL(mg_coarsen_kernel, level_grid(lv[l + 1], batch), dim3(kRedThreads), 0, st, lv[l], lv[l + 1]);
-  for (int l = 0; l < nlev; ++l)
-    hipLaunchKernelGGL(mg_diag_kernel, level_grid(lv[l], batch), dim3(kRedThreads), 0, st, lv[l]);
-  return hipGetLastError();
-}
-
-hipError_t launch_cg_start(const float* rhs, const TvCg& c, const MgLevel* lv, int nlev, int nx, int ny, int batch,
-                           hipStream_t st) {
-  hipLaunchKernelGGL(cg_start_kernel, dim3(kRedBlocks, batch), dim3(kRedThreads), 0, st, rhs, c, nx, ny);
-  hipError_t e = launch_vcycle(lv, nlev, batch, st);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(cg_rz_kernel, dim3(kRedBlocks, batch), dim3(kRedThreads), 0, st, c, nx, ny, 1);
-  hipLaunchKernelGGL(cg_start_total_kernel, dim3(batch), dim3(kRedThreads), 0, st, c);
-  return hipGetLastError();
-}
-
-hipError_t launch_cg_iteration(const TvCg& c, const MgLevel* lv, int nlev, int nx, int ny, int batch, double gamma,
-                               int par, double tol2, hipStream_t st) {
-  hipLaunchKernelGGL(cg_q_kernel, dim3(kRedBlocks, batch), dim3(kRedThreads), 0, st, c, nx, ny, gamma);
-  hipLaunchKernelGGL(cg_update_kernel, dim3(kRedBlocks, batch), dim3(kRedThreads), 0, st, c, nx, ny, par, tol2);
-  hipError_t e = launch_vcycle(lv, nlev, batch, st);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(cg_rz_kernel, dim3(kRedBlocks, batch), dim3(kRedThreads), 0, st, c, nx, ny, 0);
-  hipLaunchKernelGGL(cg_dir_kernel, dim3(kRedBlocks, batch), dim3(kRedThreads), 0, st, c, nx, ny, par, tol2);
-  return hipGetLastError();
-}
-
-// publishes the last r.r (the convergence test reads rr) and writes the solution
-hipError_t launch_cg_finish(const TvCg& c, float* out, int nx, int ny, int batch, hipStream_t st) {
-  hipLaunchKernelGGL(cg_finish_kernel, dim3(kRedBlocks, batch), dim3(kRedThreads), 0, st, c, out, nx, ny);
-  return hipGetLastError();
-}
+hipError_t tv_allow_lds() { return TvLevels::allow_lds(); }
 
 hipError_t launch_axpby(int64_t n, float a, const float* x, float b, float* y, hipStream_t st) {
   int64_t blocks = (n + kRedThreads - 1) / kRedThreads;
