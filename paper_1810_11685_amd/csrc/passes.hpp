@@ -18,6 +18,8 @@
 // places consecutive tiles of one item on the same XCD.
 #pragma once
 
+#include <type_traits>
+
 #include "qpat_internal.hpp"
 
 // Row and column lengths with compile-time kernel instances.
@@ -978,32 +980,76 @@ __device__ __forceinline__ void sensor_scatter(const Medium& M, const TapStage& 
 // ---------------------------------------------------------------- block -> (item, tile)
 // Uniform launches (all items are vectors of one plan) carry the medium in
 // the kernel arguments and find their work buffers by a fixed stride, so the
-// first global loads of a block are its data; other launches read (item,
-// tile) from a block map and the item descriptors from device memory.
+// first global loads of a block are its data; other launches read the item
+// descriptors from device memory, and (item, tile) from a block map unless all
+// items have the same number of tiles (ntile > 0).
 // Either way consecutive tiles of one item are placed on one XCD.
 template <bool U>
 __device__ __forceinline__ bool locate(const Launch& L, int ntile, int chunk, int& item, int& tile) {
-  if constexpr (U) {
+  if (U || ntile > 0) {
     const int b = blockIdx.x;
     const int i = (b & (kXcds - 1)) * chunk + (b / kXcds);
     if (i >= L.nitems * ntile) return false;
     item = i / ntile;
     tile = i - item * ntile;
     return true;
-  } else {
-    const int2 bm = L.map[blockIdx.x];
-    item = bm.x;
-    tile = bm.y;
-    return bm.x >= 0;
   }
+  const __attribute__((address_space(4))) int2* bm = (const __attribute__((address_space(4))) int2*)L.map + blockIdx.x;
+  item = bm->x;
+  tile = bm->y;
+  return item >= 0;
 }
 
+// The descriptors of a table launch are constant while a kernel runs: read
+// through the constant address space they come by scalar loads whatever the
+// kernel does in between, and their pointers, marked as global ones, give
+// global loads (the plain structure in memory gave flat loads, which wait for
+// the LDS counter too).  Fields that a pass does not use are not loaded.
+typedef const __attribute__((address_space(4))) Item ConstItem;
+typedef const __attribute__((address_space(4))) IO ConstIO;
+template <typename T>
+__device__ __forceinline__ T* as_global(T* p) {
+  return (T*)(__attribute__((address_space(1))) T*)p;
+}
 template <bool U>
-__device__ __forceinline__ const Medium& medium_of(const Launch& L, int item) {
-  if constexpr (U)
+using MediumOf = std::conditional_t<U, const Medium&, Medium>;
+template <bool U>
+using IOOf = std::conditional_t<U, const IO&, IO>;
+template <bool U>
+__device__ __forceinline__ MediumOf<U> medium_of(const Launch& L, int item) {
+  if constexpr (U) {
     return L.m;
-  else
-    return L.items[item].m;
+  } else {
+    ConstItem* t = (ConstItem*)L.items + item;
+    Medium m;
+#define QPAT_V(f) m.f = t->m.f
+#define QPAT_P(f) m.f = as_global(t->m.f)
+    QPAT_V(nx), QPAT_V(ny), QPAT_V(nxh), QPAT_V(nt), QPAT_V(ns), QPAT_V(lossy), QPAT_V(dt), QPAT_V(ypow);
+    QPAT_V(rt), QPAT_V(ct), QPAT_V(lrt), QPAT_V(lct), QPAT_V(srt), QPAT_V(lsrt), QPAT_V(rthr), QPAT_V(cthr);
+    QPAT_V(radx), QPAT_V(rady), QPAT_V(nstx), QPAT_V(nsty);
+    QPAT_P(c2), QPAT_P(c2eta), QPAT_P(c2tau), QPAT_P(rho0), QPAT_P(bx), QPAT_P(by);
+    QPAT_P(avx), QPAT_P(arx), QPAT_P(avy), QPAT_P(ary);
+    QPAT_P(dxp), QPAT_P(dxm), QPAT_P(dyp), QPAT_P(dym);
+    QPAT_P(kap), QPAT_P(ldis), QPAT_P(labs), QPAT_P(twx), QPAT_P(twy), QPAT_P(twyr);
+    QPAT_P(tap_off), QPAT_P(taps), QPAT_P(node_off), QPAT_P(nodes), QPAT_P(scon);
+#undef QPAT_V
+#undef QPAT_P
+    return m;
+  }
+}
+__device__ __forceinline__ Work table_work(const Launch& L, int item) {
+  ConstItem* t = (ConstItem*)L.items + item;
+  return Work{as_global(t->w.f0), as_global(t->w.f1), as_global(t->w.f2), as_global(t->w.f3),
+              as_global(t->w.q),  as_global(t->w.s0), as_global(t->w.s1), as_global(t->w.part)};
+}
+template <bool U>
+__device__ __forceinline__ IOOf<U> io_of(const Launch& L, int item) {
+  if constexpr (U) {
+    return L.io[item];
+  } else {
+    ConstIO* t = (ConstIO*)L.io + item;
+    return IO{as_global(t->in), as_global(t->out), as_global(t->sens), as_global(t->gc)};
+  }
 }
 
 __device__ __forceinline__ Work shift_work(const Work& w, long long off) {
@@ -1026,49 +1072,72 @@ __device__ __forceinline__ Work shift_work(const Work& w, long long off) {
 // two or three dependent round trips before a block's first data load.  These
 // empty asm statements take the fields the prologue and the load phase of a
 // uniform launch need (and the block size, an implicit argument) as SGPR
-// operands, so their loads issue as one batch at the top of the kernel.  (Table launches read their medium from the item
-// table in global memory after locating the item.)
+// operands, so their loads issue as one batch at the top of the kernel.  Table
+// launches read the same fields from the item table, as one batch once the item
+// is located.
+__device__ __forceinline__ void launch_args_batch(const Launch& L, int ntile, int chunk, int n, int flags) {
+  asm volatile("" ::"s"(ntile), "s"(chunk), "s"(n), "s"(flags), "s"(L.nitems), "s"(L.wstride), "s"(L.map),
+               "s"(L.items), "s"(L.io), "s"(blockDim.x));
+}
+// (one statement: the loads of a later one would wait for the earlier)
+#define QPAT_ROW_FIELDS(m)                                                                                   \
+  "s"(m.nx), "s"(m.nxh), "s"(m.nt), "s"(m.rt), "s"(m.ct), "s"(m.lrt), "s"(m.lct), "s"(m.twx), "s"(m.srt), \
+      "s"(m.lsrt)
 template <int BM>
-__device__ __forceinline__ void row_args_batch(const Launch& L, int ntile, int chunk, int n, int flags) {
-  const Medium& m = L.m;
-  const Work& w = L.w0;
-  asm volatile("" ::"s"(ntile), "s"(chunk), "s"(n), "s"(flags), "s"(L.nitems), "s"(L.wstride), "s"(m.nx),
-               "s"(m.nxh), "s"(m.nt), "s"(m.rt), "s"(m.ct), "s"(m.lrt), "s"(m.lct), "s"(m.twx), "s"(blockDim.x));
-  asm volatile("" ::"s"(m.srt), "s"(m.lsrt));
+__device__ __forceinline__ void row_fields_batch(const Medium& m, const Work& w) {
   if constexpr (BM == RM_F1 || BM == RM_A3) {
-    asm volatile("" ::"s"(w.s0), "s"(w.s1), "s"(w.f0), "s"(w.f1), "s"(m.bx), "s"(m.by), "s"(m.avx), "s"(m.avy));
+    asm volatile("" ::QPAT_ROW_FIELDS(m), "s"(w.s0), "s"(w.s1), "s"(w.f0), "s"(w.f1), "s"(m.bx), "s"(m.by), "s"(m.avx), "s"(m.avy));
   } else if constexpr (BM == RM_F2 || BM == RM_F2L) {
-    asm volatile("" ::"s"(w.s0), "s"(w.s1), "s"(w.f2), "s"(w.f3), "s"(m.rho0), "s"(m.arx), "s"(m.ary), "s"(m.c2),
+    asm volatile("" ::QPAT_ROW_FIELDS(m), "s"(w.s0), "s"(w.s1), "s"(w.f2), "s"(w.f3), "s"(m.rho0), "s"(m.arx), "s"(m.ary), "s"(m.c2),
                  "s"(m.tap_off));
   } else if constexpr (BM == RM_F3) {
-    asm volatile("" ::"s"(w.s0), "s"(w.s1), "s"(w.f2), "s"(w.f3), "s"(m.c2), "s"(m.c2eta), "s"(m.c2tau),
+    asm volatile("" ::QPAT_ROW_FIELDS(m), "s"(w.s0), "s"(w.s1), "s"(w.f2), "s"(w.f3), "s"(m.c2), "s"(m.c2eta), "s"(m.c2tau),
                  "s"(m.tap_off));
   } else if constexpr (BM == RM_A1) {
-    asm volatile("" ::"s"(w.s0), "s"(w.part), "s"(m.c2), "s"(m.c2eta), "s"(m.c2tau), "s"(m.tap_off),
+    asm volatile("" ::QPAT_ROW_FIELDS(m), "s"(w.s0), "s"(w.part), "s"(m.c2), "s"(m.c2eta), "s"(m.c2tau), "s"(m.tap_off),
                  "s"(m.taps), "s"(m.ny), "s"(m.ns), "s"(m.node_off), "s"(m.nodes), "s"(m.scon));
   } else if constexpr (BM == RM_A1L) {
-    asm volatile("" ::"s"(w.s0), "s"(w.f2), "s"(w.f3), "s"(m.c2), "s"(m.rho0), "s"(m.arx), "s"(m.ary),
+    asm volatile("" ::QPAT_ROW_FIELDS(m), "s"(w.s0), "s"(w.f2), "s"(w.f3), "s"(m.c2), "s"(m.rho0), "s"(m.arx), "s"(m.ary),
                  "s"(m.tap_off), "s"(m.node_off), "s"(m.nodes));
   } else if constexpr (BM == RM_A2) {
-    asm volatile("" ::"s"(w.s0), "s"(w.s1), "s"(w.q), "s"(w.f2), "s"(w.f3), "s"(m.rho0), "s"(m.arx), "s"(m.ary));
+    asm volatile("" ::QPAT_ROW_FIELDS(m), "s"(w.s0), "s"(w.s1), "s"(w.q), "s"(w.f2), "s"(w.f3), "s"(m.rho0), "s"(m.arx), "s"(m.ary));
   } else {
-    asm volatile("" ::"s"(w.s0));
+    asm volatile("" ::QPAT_ROW_FIELDS(m), "s"(w.s0));
   }
 }
 
+#undef QPAT_ROW_FIELDS
+template <int BM>
+__device__ __forceinline__ void row_args_batch(const Launch& L, int ntile, int chunk, int n, int flags) {
+  asm volatile("" ::"s"(ntile), "s"(chunk), "s"(n), "s"(flags), "s"(L.nitems), "s"(L.wstride), "s"(L.m.nx),
+               "s"(L.m.nxh), "s"(L.m.nt), "s"(L.m.rt), "s"(L.m.ct), "s"(L.m.lrt), "s"(L.m.lct), "s"(L.m.twx),
+               "s"(blockDim.x));
+  row_fields_batch<BM>(L.m, L.w0);
+}
+
+#define QPAT_COL_FIELDS(m)                                                                                  \
+  "s"(m.ny), "s"(m.nxh), "s"(m.nt), "s"(m.srt), "s"(m.ct), "s"(m.lsrt), "s"(m.lct), "s"(w.s0), "s"(w.s1), \
+      "s"(m.twy), "s"(m.twyr)
+template <int CM>
+__device__ __forceinline__ void col_fields_batch(const Medium& m, const Work& w) {
+  if constexpr (CM == CM_FRAC) {
+    asm volatile("" ::QPAT_COL_FIELDS(m), "s"(m.ldis), "s"(m.labs));
+  } else if constexpr (CM == CM_GRADP1 || CM == CM_GRADP2) {
+    asm volatile("" ::QPAT_COL_FIELDS(m), "s"(m.kap), "s"(m.dxp), "s"(m.dyp));
+  } else if constexpr (CM == CM_GRADM2 || CM == CM_DIVM) {
+    asm volatile("" ::QPAT_COL_FIELDS(m), "s"(m.kap), "s"(m.dxm), "s"(m.dym));
+  } else {
+    asm volatile("" ::QPAT_COL_FIELDS(m));
+  }
+}
+#undef QPAT_COL_FIELDS
 template <int CM>
 __device__ __forceinline__ void col_args_batch(const Launch& L, int ntile, int chunk, int n) {
   const Medium& m = L.m;
   asm volatile("" ::"s"(ntile), "s"(chunk), "s"(n), "s"(L.nitems), "s"(L.wstride), "s"(m.ny), "s"(m.nxh),
                "s"(m.nt), "s"(m.srt), "s"(m.ct), "s"(m.lsrt), "s"(m.lct), "s"(L.w0.s0), "s"(L.w0.s1), "s"(m.twy),
                "s"(m.twyr), "s"(blockDim.x));
-  if constexpr (CM == CM_FRAC) {
-    asm volatile("" ::"s"(m.ldis), "s"(m.labs));
-  } else if constexpr (CM == CM_GRADP1 || CM == CM_GRADP2) {
-    asm volatile("" ::"s"(m.kap), "s"(m.dxp), "s"(m.dyp));
-  } else if constexpr (CM == CM_GRADM2 || CM == CM_DIVM) {
-    asm volatile("" ::"s"(m.kap), "s"(m.dxm), "s"(m.dym));
-  }
+  col_fields_batch<CM>(m, L.w0);
 }
 
 // ---------------------------------------------------------------- row pass
@@ -1094,11 +1163,13 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
   constexpr bool XS = (MODE & RM_X) != 0;
   extern __shared__ float2 lds[];
   if constexpr (U) row_args_batch<BM>(L, ntile, chunk, n, flags);
+  else launch_args_batch(L, ntile, chunk, n, flags);
   int item, tile;
   if (!locate<U>(L, ntile, chunk, item, tile)) return;
-  const Medium& M = medium_of<U>(L, item);
-  const Work W = U ? shift_work(L.w0, item * L.wstride) : L.items[item].w;
-  const IO& X = L.io[item];
+  const MediumOf<U> M = medium_of<U>(L, item);
+  const Work W = U ? shift_work(L.w0, item * L.wstride) : table_work(L, item);
+  if constexpr (!U) row_fields_batch<BM>(M, W);
+  const IOOf<U> X = io_of<U>(L, item);
   if (n > M.nt - 2) return;  // this problem has finished (uneven batches)
   const int nx = row_len<NF>(M), nxh = row_half<NF>(M), rt = M.rt;
   const int y0 = tile * rt;
@@ -2515,10 +2586,12 @@ col_kernel(const Launch L, int ntile, int chunk, int mcode_arg, int n) {
   const int mcode = CM == CM_APPLY ? mcode_arg : kColCode[CM];
   extern __shared__ float2 lds[];
   if constexpr (U) col_args_batch<CM>(L, ntile, chunk, n);
+  else launch_args_batch(L, ntile, chunk, n, mcode_arg);
   int item, tile;
   if (!locate<U>(L, ntile, chunk, item, tile)) return;
-  const Medium& M = medium_of<U>(L, item);
-  const Work W = U ? shift_work(L.w0, item * L.wstride) : L.items[item].w;
+  const MediumOf<U> M = medium_of<U>(L, item);
+  const Work W = U ? shift_work(L.w0, item * L.wstride) : table_work(L, item);
+  if constexpr (!U) col_fields_batch<CM>(M, W);
   if (n > M.nt - 2) return;  // this problem has finished (uneven batches)
   // Lengths with a compile-time plan take the fused pass, in their own
   // instance or (launches over several lengths) in the all-length one; the

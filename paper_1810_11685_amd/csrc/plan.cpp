@@ -264,6 +264,7 @@ struct Exec {
   bool uniform = false;
   int row_ntile = 0, col_ntile = 0, row_chunk = 0, col_chunk = 0;
   int tab_nx = 0, tab_ny = 0;  // table launches: the row / column length all items share (0: they differ)
+  bool tab_rows = false, tab_cols = false;  // table launches: all items have the same number of row / column tiles
   bool row_tg = false, col_tg = false;  // uniform launches: FFT twiddles read from global memory
   bool lossy = false;
   // pinned staging ring for the I/O table
@@ -370,6 +371,11 @@ qpat_status exec_build(Exec& E, const std::vector<Item>& items) {
     E.L.nitems = ni;
     E.row_ntile = m0.ny / m0.rt;
     E.col_ntile = m0.nxh / m0.ct;
+    E.tab_rows = E.tab_cols = !u;
+    for (int i = 1; i < ni; ++i) {
+      E.tab_rows = E.tab_rows && items[i].m.ny / items[i].m.rt == E.row_ntile;
+      E.tab_cols = E.tab_cols && items[i].m.nxh / items[i].m.ct == E.col_ntile;
+    }
     E.row_chunk = (ni * E.row_ntile + kXcds - 1) / kXcds;
     E.col_chunk = (ni * E.col_ntile + kXcds - 1) / kXcds;
     // Twiddles from global memory when a pass has at most about two blocks
@@ -438,7 +444,9 @@ hipError_t row(Exec& E, int mode, int n, int flags, hipStream_t st) {
                       E.row_lds, n, flags, st);
   Launch L = E.L;
   L.map = E.d_rowmap;
-  return launch_row(mode, L, false, E.tab_nx, false, 0, 0, E.nrow, E.rthr, E.row_lds, n, flags, st);
+  const int nt = E.tab_rows ? E.row_ntile : 0;
+  return launch_row(mode, L, false, E.tab_nx, false, nt, E.row_chunk, nt ? E.row_chunk * kXcds : E.nrow, E.rthr,
+                    E.row_lds, n, flags, st);
 }
 hipError_t col(Exec& E, int cm, int n, hipStream_t st, int mcode = 0) {
   if (E.uniform)
@@ -446,7 +454,9 @@ hipError_t col(Exec& E, int cm, int n, hipStream_t st, int mcode = 0) {
                       E.col_lds, n, st);
   Launch L = E.L;
   L.map = E.d_colmap;
-  return launch_col(cm, mcode, L, false, E.tab_ny, false, 0, 0, E.ncol, E.cthr, E.col_lds, n, st);
+  const int nt = E.tab_cols ? E.col_ntile : 0;
+  return launch_col(cm, mcode, L, false, E.tab_ny, false, nt, E.col_chunk, nt ? E.col_chunk * kXcds : E.ncol, E.cthr,
+                    E.col_lds, n, st);
 }
 
 #define LCHK(expr)                           \
