@@ -231,6 +231,24 @@ void table_tiles(int nx, int ny, int* rt, int* ct, int* rthr, int* cthr) {
   *cthr = cthr_;
 }
 
+// Launch shape of c problems of one size, launched beside those of other sizes:
+// one problem has the shape of a single vector (its launch is a uniform one);
+// more have blocks of two rows and one column, with the threads of a table
+// launch, up to kManyBlocks of them.  A J^T J v of the batch, ms, with
+// table_tiles for all -> this: one problem each of 256^2, 384^2 and 512^2 18.9 ->
+// 17.5, 192^2 and two 512^2 18.6 -> 16.6, seven of 256^2 to 512^2 22.1 -> 21.7, six
+// of 256^2 13.7 -> 13.0, twenty of 256^2 to 512^2 32.9 both ways (two rows up to
+// twice as many blocks: 33.3; always: 35.8).
+void group_tiles(int nx, int ny, int c, int* rt, int* ct, int* rthr, int* cthr) {
+  if (c == 1) return auto_tiles(nx, ny, 1, rt, ct, rthr, cthr);
+  table_tiles(nx, ny, rt, ct, rthr, cthr);
+  if (c * (ny / 2) <= kManyBlocks && row_tile_ok(nx, ny, 2, 256)) *rt = 2, *rthr = 256;
+  if (c * (nx / 2) <= kManyBlocks && col_tile_ok(nx / 2, ny, 1, *cthr)) {
+    *ct = 1;
+    while (*cthr > 64 && *cthr * 4 > ny && col_tile_ok(nx / 2, ny, 1, *cthr / 2)) *cthr /= 2;
+  }
+}
+
 // The launch shape as the kernels read it.
 void shape_medium(Medium& m, int rt, int ct, int rthr, int cthr) {
   m.rt = rt;
@@ -572,12 +590,14 @@ struct qpat_plan_s {
   bool graph = false;
   bool auto_shape = true;   // the launch shape follows the batch size until set_tiles / tune
   int rt = 2, ct = 1, rthr = kBlock, cthr = kBlock;   // the fixed shape (auto: the one of a single vector)
-  // the medium with the launch shape for b vectors (b = 0: for a table launch)
+  // the medium with the launch shape for b vectors (b = 0: for a launch over
+  // several grid sizes, b < 0: of -b problems of this size beside others)
   Medium medium_for(int b) const {
     Medium m = med;
     if (auto_shape) {
       int r, c, rh, ch;
       if (b > 0) auto_tiles(prm.nx, prm.ny, b, &r, &c, &rh, &ch);
+      else if (b < 0) group_tiles(prm.nx, prm.ny, -b, &r, &c, &rh, &ch);
       else table_tiles(prm.nx, prm.ny, &r, &c, &rh, &ch);
       shape_medium(m, r, c, rh, ch);
     }
@@ -606,8 +626,14 @@ struct qpat_batch_s {
   std::vector<std::unique_ptr<Group>> groups;
   int schedule = 0;
   hipEvent_t fork = nullptr;
-  bool graph = false;   // each group's sequence replays from its executor's graph
+  bool graph = false;
+  std::map<int, std::pair<hipGraph_t, hipGraphExec_t>> graphs;  // whole fork/join sequences, by operation
   void release_groups() {
+    for (auto& g : graphs) {
+      if (g.second.second) (void)hipGraphExecDestroy(g.second.second);
+      if (g.second.first) (void)hipGraphDestroy(g.second.first);
+    }
+    graphs.clear();
     for (auto& g : groups) {
       g->exec.release();
       if (g->stream) (void)hipStreamDestroy(g->stream);
@@ -1716,7 +1742,7 @@ static qpat_status batch_build(qpat_batch B) {
     g->members = mem;
     std::vector<Item> items(mem.size());
     for (size_t k = 0; k < mem.size(); ++k) {
-      items[k].m = B->plans[mem[k]]->medium_for(0);
+      items[k].m = B->plans[mem[k]]->medium_for(B->schedule == 0 ? 0 : -int(mem.size()));
       items[k].w = B->works[mem[k]];
     }
     STCHK(exec_build(g->exec, items));
@@ -1780,25 +1806,43 @@ static qpat_status batch_io(qpat_batch B, const float* const* in, float* const* 
 }
 
 // The forward or adjoint sweep of every group: on `st` for one group, else
-// forked onto the groups' streams and joined back into `st`.  In graph mode a
-// group replays a graph of its own: a graph of all groups, with its parallel
-// branches, takes the host about 4 us a node (7 problems of 256^2 to 512^2, 80
-// to 160 steps, 4320 launches: 22.6 ms, with a graph per group 19.5; 3 problems
-// 19.3 -> 15.6, 20 problems 32.8 -> 29.8).  Groups with more time steps start
-// first.
-static qpat_status batch_run(qpat_batch B, int op, hipStream_t st) {
-  if (B->groups.size() == 1) return exec_run(B->groups[0]->exec, op, B->graph, st);
-  std::vector<qpat_batch_s::Group*> order;
-  for (auto& g : B->groups) order.push_back(g.get());
-  std::stable_sort(order.begin(), order.end(),
-                   [](const auto* a, const auto* b) { return a->exec.max_nt > b->exec.max_nt; });
-  HIPCHK(hipEventRecord(B->fork, st));
-  for (auto* g : order) {
-    HIPCHK(hipStreamWaitEvent(g->stream, B->fork, 0));
-    STCHK(exec_run(g->exec, op, B->graph, g->stream));
-    HIPCHK(hipEventRecord(g->done, g->stream));
+// forked onto the groups' streams and joined back into `st`.
+static hipError_t batch_body(qpat_batch B, int op, hipStream_t st) {
+  auto sweep = [&](Exec& E, hipStream_t s) {
+    return op == OP_FWD ? seq_forward(E, E.max_nt - 2, s) : seq_adjoint(E, s);
+  };
+  if (B->groups.size() == 1) return sweep(B->groups[0]->exec, st);
+  LCHK(hipEventRecord(B->fork, st));
+  for (auto& g : B->groups) {
+    LCHK(hipStreamWaitEvent(g->stream, B->fork, 0));
+    LCHK(sweep(g->exec, g->stream));
+    LCHK(hipEventRecord(g->done, g->stream));
   }
-  for (auto* g : order) HIPCHK(hipStreamWaitEvent(st, g->done, 0));
+  for (auto& g : B->groups) LCHK(hipStreamWaitEvent(st, g->done, 0));
+  return hipSuccess;
+}
+
+static qpat_status batch_run(qpat_batch B, int op, hipStream_t st) {
+  if (!B->graph || st == nullptr) {
+    hipError_t e = batch_body(B, op, st);
+    if (e != hipSuccess) return fail(QPAT_E_HIP, std::string("kernel launch: ") + hipGetErrorString(e));
+    return QPAT_OK;
+  }
+  auto it = B->graphs.find(op);
+  if (it == B->graphs.end()) {
+    hipGraph_t g = nullptr;
+    hipGraphExec_t ge = nullptr;
+    HIPCHK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
+    hipError_t e = batch_body(B, op, st);
+    hipError_t e2 = hipStreamEndCapture(st, &g);
+    if (e != hipSuccess || e2 != hipSuccess) {
+      if (g) (void)hipGraphDestroy(g);
+      return fail(QPAT_E_HIP, std::string("graph capture: ") + hipGetErrorString(e != hipSuccess ? e : e2));
+    }
+    HIPCHK(hipGraphInstantiate(&ge, g, nullptr, nullptr, 0));
+    it = B->graphs.emplace(op, std::make_pair(g, ge)).first;
+  }
+  HIPCHK(hipGraphLaunch(it->second.second, st));
   return QPAT_OK;
 }
 

@@ -110,3 +110,27 @@ def test_shape_chosen_per_batch_size_is_bitwise(q, nx, ny, b):
     plan.set_tiles(*one)               # fixed from here on, the same shape for every count
     assert plan.tiles() == one
     assert np.array_equal(N(plan.jtjv(x)), many)
+
+
+def test_launch_sequence_per_size_bitwise(q):
+    """One launch sequence per grid size: groups of one problem (the shape of a
+    single vector), of a few (two rows, one column a block) and, of 1024-point
+    lines, of more blocks than four per CU along one axis."""
+    import torch
+    probs = []
+    for i, (nx, ny) in enumerate([(96, 96), (64, 64), (64, 64)] + [(32, 1024)] * 3 + [(1024, 32)] * 3):
+        prm, c0, rho0, _ = problem(nx, ny, 8 + i % 3, 0.75)
+        probs.append((q.Plan(prm, c0 * (1 - 0.005 * i), rho0 * (1 + 0.005 * i)), T(qi.gaussian_field((ny, nx), 20 + i))))
+    xs = [x for _, x in probs]
+    refs = [N(plan.jtjv(x)) for plan, x in probs]
+    bat = q.Batch([plan for plan, _ in probs])
+    bat.set_schedule(1)
+    for ref, g in zip(refs, bat.jtjv(xs)):
+        assert np.array_equal(N(g), ref)
+    bat.set_graph(True)
+    s = torch.cuda.Stream()
+    for _ in range(2):
+        out = bat.jtjv(xs, stream=s)
+        s.synchronize()
+        for ref, g in zip(refs, out):
+            assert np.array_equal(N(g), ref)
