@@ -8,8 +8,10 @@
 //                z-FFTs, the k-space multiplier, inverse z- and y-FFTs.
 // The FFTs are mixed-radix Stockham transforms in LDS with a runtime plan per
 // axis: radices 2, 3, 4, 5, 7, 8 as butterflies, any other prime factor as a
-// direct DFT stage, so axis lengths such as 33, 37, 49 and 53 of the paper's
-// 3-D grids (with their PML) run without padding.
+// direct DFT stage, so any length runs without padding.  Axes of 18 to 63 points
+// are transformed as matrix products instead (k3d_dense.hip; dense3 and
+// dense3_plane say which); 49 x 49 planes and 64-point axes have compile-time
+// stages.
 #include "k3d_device.hpp"
 
 namespace qpat3 {

@@ -214,8 +214,7 @@ void auto_tiles(int nx, int ny, int b, int* rt, int* ct, int* rthr, int* cthr) {
 // about 2048 elements, 256 threads, whatever the number of problems.  A launch
 // over several grid sizes runs with the largest thread count and LDS of its
 // problems, so small blocks of 512 threads cost it (7 problems of 256^2 to
-// 512^2 in one launch set: 25.5 ms, with the shapes above 37.5; one launch
-// sequence per size: 22.8 either way).
+// 512^2 in one launch set: 25.5 ms, with the shapes above 37.5).
 void table_tiles(int nx, int ny, int* rt, int* ct, int* rthr, int* cthr) {
   int r = 2;
   while (r < 16 && r * nx < 2048 && row_tile_ok(nx, ny, 2 * r, 256)) r *= 2;
