@@ -69,15 +69,17 @@ KERNEL_OF_PASS = {4: "col_fraclap", 7: "col_fraclap"}
 
 
 # Algorithmic HBM bytes per FEM node of one conjugate-gradient iteration of
-# the optical solve (FP64), as its kernels are fused.  Level 0: direction and
-# product read z, p and the 4-array stencil (48) and write p, q (16); the update
-# with the first restriction reads x, p, r, q, the inverse diagonal and the
-# stencil (72) and writes x, r and a quarter of a coarse value (18); correction
-# and post-sweep read r, the inverse diagonal, the stencil (48) and a quarter of
-# a coarse value (2) and write z (8).  The other levels, a third of level 0's
-# nodes in all (the smallest ones in LDS): 50 down and 58 up.
-OPT_CG_BYTES = 64.0 + 90.0 + 58.0
-OPT_VCYCLE_BYTES = (50.0 + 58.0) / 3.0
+# the optical solve (FP64).  CG: A p reads p and the two elemental
+# coefficients of the pixel it owns (8 + 32) and writes q (8); the update
+# reads x, p, r, q (32) and writes x, r (16); r.z reads r, z (16); the new
+# direction reads z, p (16) and writes p (8).  V-cycle, per node of a level
+# (the first sweep's x = om dinv b is recomputed, not stored): the
+# restriction reads b, the inverse diagonal and the 4-array stencil (48) and
+# writes a quarter of a coarse value (2); correction and post-sweep read the
+# same (48) and a quarter of a coarse value (2) and write t (8).  The levels
+# add up to 4/3 of the fine grid's nodes.
+OPT_CG_BYTES = 48.0 + 48.0 + 16.0 + 24.0
+OPT_VCYCLE_BYTES = (50.0 + 58.0) * 4.0 / 3.0
 OPT_BYTES_PER_NODE_ITER = OPT_CG_BYTES + OPT_VCYCLE_BYTES
 
 
