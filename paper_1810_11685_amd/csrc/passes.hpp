@@ -1004,7 +1004,9 @@ __device__ __forceinline__ bool locate(const Launch& L, int ntile, int chunk, in
 // through the constant address space they come by scalar loads whatever the
 // kernel does in between, and their pointers, marked as global ones, give
 // global loads (the plain structure in memory gave flat loads, which wait for
-// the LDS counter too).  Fields that a pass does not use are not loaded.
+// the LDS counter too).  Fields that a pass does not use are not loaded.  Seven
+// problems of 256^2 to 512^2, a launch sequence per size: 29.7 -> 27.8 ms (column
+// passes of three 256^2 6.7 -> 6.2 us, row passes 8.8 -> 8.4).
 typedef const __attribute__((address_space(4))) Item ConstItem;
 typedef const __attribute__((address_space(4))) IO ConstIO;
 template <typename T>
