@@ -152,12 +152,16 @@ __device__ __forceinline__ void stockham(const float2* src, float2* dst, int j, 
   for (int r = 0; r < R; ++r) dst[px(base + r * Ns)] = v[r];
 }
 
-// Forward FFT of `nlines` lines of length n (line stride ls) held in LDS
-// buffer a, using b as the ping-pong partner and the twiddle table tw (LDS).
-// The radix plans keep Ns a power of two in every stage but the last.  All
-// threads of the block take part; returns the buffer
-// that holds the result.  The caller must have synchronised after writing the
-// input; the routine ends synchronised.
+// Forward FFT of `nlines` lines (line stride ls) held in LDS buffer a, of a
+// length n without kernels of its own: 8 to 24, radices 2, 3, 4 and 8.  b is
+// the ping-pong partner and tw the twiddle table (LDS).  The radix plans keep
+// Ns a power of two in every stage but the last.  All threads of the block take
+// part; returns the buffer that holds the result.  The caller must have
+// synchronised after writing the input; the routine ends synchronised.
+// (With the radix 6 and 12 stages of the longer lengths in here, every kernel
+// that calls it took 20 to 80 registers more: 3 waves a SIMD instead of 4 to 8,
+// and a J^T J v of 60 steps 4.19 ms instead of 3.31 at 8 x 8, 5.24 instead of 4.27
+// at 24 x 24.)
 __device__ float2* fft_lines(float2* a, float2* b, int nlines, int n, int ls, uint32_t rad, int nst,
                              const float2* tw) {
   int Ns = 1;
@@ -179,12 +183,8 @@ __device__ float2* fft_lines(float2* a, float2* b, int nlines, int n, int ls, ui
         stockham<4>(src, dst, j, nb, Ns, off, tw);
       else if (R == 2)
         stockham<2>(src, dst, j, nb, Ns, off, tw);
-      else if (R == 3)
-        stockham<3>(src, dst, j, nb, Ns, off, tw);
-      else if (R == 6)
-        stockham<6>(src, dst, j, nb, Ns, off, tw);
       else
-        stockham<12>(src, dst, j, nb, Ns, off, tw);
+        stockham<3>(src, dst, j, nb, Ns, off, tw);
     }
     __syncthreads();
     float2* t = a;
@@ -602,32 +602,29 @@ __device__ __forceinline__ float2* fft_fused_pairs(float2* a, float2* b, int nli
   else return fft_stages<N, false, LS, 1, NST, R>(o, r, nlines, tw);
 }
 
-// FFT of `nlines` lines: compile-time plan for the common lengths, the
-// runtime plan otherwise.  Same contract as fft_lines; row lines have stride
-// lstride(n), column lines (COL) col_lstride(n).  IP (instances with a
-// compile-time length only, n == NF): the stages run in place in a (b unused).
-// NF != 0: a kernel instance for lines of length NF carries that compile-time
-// plan only (and the runtime plan as a fallback), so the other lengths'
-// unrolled code does not weigh on it.
-template <bool COL, int NF = 0, bool IP = false>
+// FFT of `nlines` lines, same contract as fft_lines; row lines have stride
+// lstride(n), column lines (COL) col_lstride(n).  NF != 0: an instance for lines
+// of length NF (n == NF), which carries that compile-time plan only; IP: its
+// stages run in place in a (b unused).  NF == 0: an instance for several
+// lengths, MIX of them all (a table launch), else of those without a plan of
+// their own, 8 to 24.
+template <bool COL, int NF, bool IP, bool MIX>
 __device__ __forceinline__ float2* fft_any(float2* a, float2* b, int nlines, int n, int ls, uint32_t rad,
                                            int nst, const float2* tw) {
   if constexpr (NF != 0) {
     if constexpr (IP) return fft_c_ip<NF, COL ? col_lstride(NF) : lstride(NF), 0, 1>(a, nlines, tw);
-    if (n == NF) return fft_c<NF, COL ? col_lstride(NF) : lstride(NF), 0, 1>(a, b, nlines, tw);
-    return fft_lines(a, b, nlines, n, ls, rad, nst, tw);
+    else return fft_c<NF, COL ? col_lstride(NF) : lstride(NF), 0, 1>(a, b, nlines, tw);
   } else {
+    if constexpr (MIX) {
 #define QPAT_FFT_CASE(N) \
   case N: return fft_c<N, COL ? col_lstride(N) : lstride(N), 0, 1>(a, b, nlines, tw);
-    switch (n) {
-      QPAT_FFT_CASE(128)
-      QPAT_FFT_CASE(256)
-      QPAT_FFT_CASE(384)
-      QPAT_FFT_CASE(512)
-      QPAT_FFT_CASE(1024)
-      default: return fft_lines(a, b, nlines, n, ls, rad, nst, tw);
-    }
+      switch (n) {
+        QPAT_FOR_LENGTHS(QPAT_FFT_CASE)
+        default: break;
+      }
 #undef QPAT_FFT_CASE
+    }
+    return fft_lines(a, b, nlines, n, ls, rad, nst, tw);
   }
 }
 
@@ -1283,7 +1280,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     put_pair<NF>(S, bufA, M);
     if constexpr (!TG) put_tw(TW, twl, nx);
     __syncthreads();
-    float2* r = fft_any<false, NF, IP>(bufA, bufB, rt, nx, LS, M.radx, M.nstx, tw);
+    float2* r = fft_any<false, NF, IP, !U>(bufA, bufB, rt, nx, LS, M.radx, M.nstx, tw);
     float2* o = other(r, bufA, bufB);
     // all LDS reads of the loop first: its LDS writes go to the other buffer,
     // which the compiler cannot tell, so an interleaved loop waits per element
@@ -1311,7 +1308,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
       }
     }
     __syncthreads();
-    r = fft_any<false, NF, IP>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
+    r = fft_any<false, NF, IP, !U>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
     store_pair_spectra<NF, TG>(r, M, W.s0, W.s1, tile);
   } else if constexpr (FZ) {
     // RM_FZ instances of the lossy density passes (forward eq num-rho and its
@@ -1595,7 +1592,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     float2* r = nullptr;
     float2* o = bufA;
     if (!skip) {
-      r = fft_any<false, NF, IP>(bufA, bufB, rt, nx, LS, M.radx, M.nstx, tw);
+      r = fft_any<false, NF, IP, !U>(bufA, bufB, rt, nx, LS, M.radx, M.nstx, tw);
       o = other(r, bufA, bufB);
     }
     float2 zr[kMaxPer];
@@ -1646,12 +1643,12 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     if constexpr (BM == RM_F2L) taps_put(T, false);
     __syncthreads();
     if constexpr (BM == RM_F2) {
-      r = fft_any<false, NF, IP>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
+      r = fft_any<false, NF, IP, !U>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
       store_rowpair_spectra<NF, TG>(r, M, W.s0, tile);
       store_rowpair_spectra<NF, TG>(r + (rt / 2) * LS, M, W.s1, tile);
     } else {
       if (!(flags & FL_NO_SENSORS)) sensor_partials(M, T, o, y0, W.part, n + 1);
-      r = fft_any<false, NF, IP>(o, other(o, bufA, bufB), rt / 2, nx, LS, M.radx, M.nstx, tw);
+      r = fft_any<false, NF, IP, !U>(o, other(o, bufA, bufB), rt / 2, nx, LS, M.radx, M.nstx, tw);
       store_rowpair_spectra<NF, TG>(r, M, W.s0, tile);
     }
   } else if constexpr (BM == RM_F3) {
@@ -1681,7 +1678,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     if constexpr (!TG) put_tw(TW, twl, nx);
     __syncthreads();
     taps_fetch(T, M, nullptr, 0);
-    float2* r = fft_any<false, NF, IP>(bufA, bufB, rt, nx, LS, M.radx, M.nstx, tw);
+    float2* r = fft_any<false, NF, IP, !U>(bufA, bufB, rt, nx, LS, M.radx, M.nstx, tw);
     float2* o = other(r, bufA, bufB);
     float ysr[kMaxPer], yur[kMaxPer];
     FOR_K {
@@ -1713,7 +1710,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     taps_put(T, false);
     __syncthreads();
     if (!(flags & FL_NO_SENSORS)) sensor_partials(M, T, o, y0, W.part, n + 1);
-    r = fft_any<false, NF, IP>(o, other(o, bufA, bufB), rt / 2, nx, LS, M.radx, M.nstx, tw);
+    r = fft_any<false, NF, IP, !U>(o, other(o, bufA, bufB), rt / 2, nx, LS, M.radx, M.nstx, tw);
     store_rowpair_spectra<NF, TG>(r, M, W.s0, tile);
   } else if constexpr (BM == RM_A1 || BM == RM_A1L) {
     // transpose of eqs num-m and num-p: p* += M^T r_{n+1}; q = c^2 p*
@@ -1776,7 +1773,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     nodes_fetch(T, M);
     float2* r = bufA;
     if (!first) {
-      r = fft_any<false, NF, IP>(bufA, bufB, half, nx, LS, M.radx, M.nstx, tw);
+      r = fft_any<false, NF, IP, !U>(bufA, bufB, half, nx, LS, M.radx, M.nstx, tw);
       // p* = -(grad_x^- g_x + grad_y^- g_y): negate the (conjugated) inverse
 #pragma unroll 4
       for (int it = threadIdx.x; it < half * LS; it += B) {
@@ -1829,11 +1826,11 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     }
     __syncthreads();
     if constexpr (BM == RM_A1) {
-      r = fft_any<false, NF, IP>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
+      r = fft_any<false, NF, IP, !U>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
       store_rowpair_spectra<NF, TG>(r, M, W.s0, tile);
       store_rowpair_spectra<NF, TG>(r + half * LS, M, W.s1, tile);
     } else if (n != -1) {
-      r = fft_any<false, NF, IP>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
+      r = fft_any<false, NF, IP, !U>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
       store_pair_spectra<NF, TG>(r, M, W.s0, W.s1, tile);
     }
   } else if constexpr (BM == RM_A2) {
@@ -1874,7 +1871,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     put_rowpair<NF>(S1, bufA + (rt / 2) * LS, M);
     if constexpr (!TG) put_tw(TW, twl, nx);
     __syncthreads();
-    float2* r = fft_any<false, NF, IP>(bufA, bufB, rt, nx, LS, M.radx, M.nstx, tw);
+    float2* r = fft_any<false, NF, IP, !U>(bufA, bufB, rt, nx, LS, M.radx, M.nstx, tw);
     float2* o = other(r, bufA, bufB);
     float ydr[kMaxPer], yar[kMaxPer];
     FOR_K {
@@ -1907,7 +1904,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     }
     __syncthreads();
     if (n != -1) {
-      r = fft_any<false, NF, IP>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
+      r = fft_any<false, NF, IP, !U>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
       store_pair_spectra<NF, TG>(r, M, W.s0, W.s1, tile);
     }
   } else if constexpr (BM == RM_A3) {
@@ -1934,7 +1931,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     put_pair<NF>(S, bufA, M);
     if constexpr (!TG) put_tw(TW, twl, nx);
     __syncthreads();
-    float2* r = fft_any<false, NF, IP>(bufA, bufB, rt, nx, LS, M.radx, M.nstx, tw);
+    float2* r = fft_any<false, NF, IP, !U>(bufA, bufB, rt, nx, LS, M.radx, M.nstx, tw);
     float2* o = other(r, bufA, bufB);
     float2 zr[kMaxPer];
     FOR_K {
@@ -1960,7 +1957,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
       }
     }
     __syncthreads();
-    r = fft_any<false, NF, IP>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
+    r = fft_any<false, NF, IP, !U>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
     store_pair_spectra<NF, TG>(r, M, W.s0, W.s1, tile);
   } else if constexpr (BM == RM_FWD1) {
     const float* src = X.in;
@@ -1983,7 +1980,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     }
     if constexpr (!TG) put_tw(TW, twl, nx);
     __syncthreads();
-    float2* r = fft_any<false, NF, IP>(bufA, bufB, rt / 2, nx, LS, M.radx, M.nstx, tw);
+    float2* r = fft_any<false, NF, IP, !U>(bufA, bufB, rt / 2, nx, LS, M.radx, M.nstx, tw);
     store_rowpair_spectra<NF, TG>(r, M, W.s0, tile);
   } else if constexpr (BM == RM_INV1) {
     RowPairRegs S0;
@@ -1993,7 +1990,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     put_rowpair<NF>(S0, bufA, M);
     if constexpr (!TG) put_tw(TW, twl, nx);
     __syncthreads();
-    float2* r = fft_any<false, NF, IP>(bufA, bufB, rt / 2, nx, LS, M.radx, M.nstx, tw);
+    float2* r = fft_any<false, NF, IP, !U>(bufA, bufB, rt / 2, nx, LS, M.radx, M.nstx, tw);
     float* dst = X.out;
 #pragma unroll 4
     for (int it = threadIdx.x; it < tot; it += B) {
@@ -2117,7 +2114,7 @@ __device__ __forceinline__ void col_generic(const Medium& M, const Work& W, int 
   }
   if constexpr (!TG) put_tw(TW, twl, ny);
   __syncthreads();
-  float2* r = fft_any<true, NF>(bufA, bufB, nin * ct, ny, ls, M.rady, M.nsty, tw);
+  float2* r = fft_any<true, 0, false, false>(bufA, bufB, nin * ct, ny, ls, M.rady, M.nsty, tw);
   float2* o = other(r, bufA, bufB);
 #pragma unroll
   for (int k = 0; k < kColPer; ++k) {
@@ -2177,7 +2174,7 @@ __device__ __forceinline__ void col_generic(const Medium& M, const Work& W, int 
     }
   }
   __syncthreads();
-  r = fft_any<true, NF>(o, other(o, bufA, bufB), nout * ct, ny, ls, M.rady, M.nsty, tw);
+  r = fft_any<true, 0, false, false>(o, other(o, bufA, bufB), nout * ct, ny, ls, M.rady, M.nsty, tw);
   for (unsigned it = threadIdx.x; it < nout * ncol; it += B) {
     const bool f = it >= ncol;
     const unsigned rem = f ? it - ncol : it, w = rem & (rc - 1), ty = rem >> lsh;
@@ -2596,7 +2593,7 @@ col_kernel(const Launch L, int ntile, int chunk, int mcode_arg, int n) {
   if constexpr (!U) col_fields_batch<CM>(M, W);
   if (n > M.nt - 2) return;  // this problem has finished (uneven batches)
   // Lengths with a compile-time plan take the fused pass, in their own
-  // instance or (launches over several lengths) in the all-length one; the
+  // instance or, where a table launch holds several lengths, in this one; the
   // generic pass serves the short lengths 8 to 24.
   if constexpr (NF > 0) {
     col_fused<CM, NF, TG, !TG>(M, W, tile, mcode, lds);  // in place unless twiddles are read from global memory
@@ -2605,9 +2602,11 @@ col_kernel(const Launch L, int ntile, int chunk, int mcode_arg, int n) {
   case N:                                       \
     col_fused<CM, N, TG>(M, W, tile, mcode, lds); \
     return;
-    switch (M.ny) {
-      QPAT_FOR_LENGTHS(QPAT_COL_CASE)
-      default: break;
+    if constexpr (!U) {
+      switch (M.ny) {
+        QPAT_FOR_LENGTHS(QPAT_COL_CASE)
+        default: break;
+      }
     }
 #undef QPAT_COL_CASE
     col_generic<CM, NF, TG>(M, W, tile, mcode, lds);
