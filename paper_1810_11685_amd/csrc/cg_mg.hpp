@@ -52,16 +52,36 @@ struct Vectors {
 };
 
 // ---------------------------------------------------------------- tiles
-// A block of two waves works on 32 x 16 nodes: thread (x, y) on column x, rows
-// 4 y .. 4 y + 3, so that a row of coefficients is read along x and a vertical
-// coupling once.  The iterate sits in LDS with a ring of one node (zero outside
-// the grid).  Small tiles: the coarser levels are bound by latency and gain from
-// more blocks (4 to 5 us a launch, of which 3.4 is the launch).
-constexpr int kTX = 32, kTY = 16, kRows = 4, kThreads = kTX * (kTY / kRows);
-constexpr int kHX = kTX + 2, kHY = kTY + 2, kHN = kHX * kHY, kSlots = (kHN + kThreads - 1) / kThreads;
+// A block of two waves works on a tile of 512 nodes, TX x 512 / TX: thread (x, y)
+// on column x, rows 4 y .. 4 y + 3, so that a row of coefficients is read along x
+// and a vertical coupling once.  The iterate sits in LDS with a ring of one node
+// (zero outside the grid).  Small tiles: the coarser levels are bound by latency
+// and gain from more blocks (4 to 5 us a launch, of which 3.4 is the launch).
+constexpr int kRows = 4, kThreads = 128, kTileNodes = kThreads * kRows;
+template <int TX_>
+struct Tile {
+  static constexpr int TX = TX_, TY = kTileNodes / TX, HX = TX + 2, HY = TY + 2, HN = HX * HY;
+  static constexpr int SLOTS = (HN + kThreads - 1) / kThreads;
+};
 
-inline int tiles_x(int nx) { return (nx + kTX - 1) / kTX; }
-inline int tiles(int nx, int ny) { return tiles_x(nx) * ((ny + kTY - 1) / kTY); }
+// The tile of a level: 32 x 16; on long strips, of which that would hold a few
+// columns or rows, 4 x 128 (up to 12 columns) or 128 x 4 (up to 4 rows).  64 fields,
+// ms a solve, 32 x 16 -> these (one thread a node, as the sweeps were launched
+// before the tiles): TV 2 x 8000 27.8 -> 8.5 (12.8), 8000 x 2 29.8 -> 14.3 (23.8);
+// optical 2 x 8000 nodes 9.0 -> 2.9 (3.1), 9 x 8000 16.1 -> 8.2 (10.1).  A strip of up
+// to 1024 nodes is bound by latency with either tile, and 13 columns or 5 rows
+// fill enough of 32 x 16.
+constexpr int kSquareTile = 32, kNarrowTile = 4, kFlatTile = 128, kStrip = 1024;
+inline int tile_width(int nx, int ny) {
+  if (nx <= 3 * kNarrowTile && ny > kStrip) return kNarrowTile;
+  if (ny <= kTileNodes / kFlatTile && nx > kStrip) return kFlatTile;
+  return kSquareTile;
+}
+inline int tiles_x(int nx, int ny) { return (nx + tile_width(nx, ny) - 1) / tile_width(nx, ny); }
+inline int tiles(int nx, int ny) {
+  const int ty = kTileNodes / tile_width(nx, ny);
+  return tiles_x(nx, ny) * ((ny + ty - 1) / ty);
+}
 // Blocks of a level, a multiple of the eight XCDs: block k runs on XCD k % 8 and
 // takes tile first_tile(), so that an XCD's tiles are neighbours and its L2 holds
 // the rings they share (a block past the last tile has none).  Level 0 of four
@@ -73,12 +93,13 @@ struct Slot {   // position s of this thread in the ringed tile
   int pos, k;
   bool in, own;
 };
+template <class T>
 __device__ __forceinline__ Slot slot(int s, int i0, int j0, int nx, int ny) {
   Slot r;
   r.pos = int(threadIdx.x) + kThreads * s;
-  const int py = r.pos / kHX, px = r.pos - kHX * py, i = i0 - 1 + px, j = j0 - 1 + py;
-  r.in = r.pos < kHN && i >= 0 && i < nx && j >= 0 && j < ny;
-  r.own = r.in && px >= 1 && px <= kTX && py >= 1 && py <= kTY;
+  const int py = r.pos / T::HX, px = r.pos - T::HX * py, i = i0 - 1 + px, j = j0 - 1 + py;
+  r.in = r.pos < T::HN && i >= 0 && i < nx && j >= 0 && j < ny;
+  r.own = r.in && px >= 1 && px <= T::TX && py >= 1 && py <= T::TY;
   r.k = r.in ? j * nx + i : 0;
   return r;
 }
@@ -114,10 +135,11 @@ __device__ __forceinline__ double tile_sum(double v) {
 }
 
 // A u at node (column x, row y) of the tile, from the ringed LDS tile
-template <class Op>
+template <class Op, class T>
 __device__ __forceinline__ double tile_op(const typename Op::Coef& C, const double* u, int x, int y) {
-  const double* c = u + (y + 1) * kHX + x + 1;
-  return Op::product(C, c[0], c[1], c[-1], c[kHX], c[-kHX], c[kHX + 1], c[-kHX - 1]);
+  constexpr int H = T::HX;
+  const double* c = u + (y + 1) * H + x + 1;
+  return Op::product(C, c[0], c[1], c[-1], c[H], c[-H], c[H + 1], c[-H - 1]);
 }
 template <class Op>
 __device__ __forceinline__ void tile_coefs(const typename Op::Level& L, size_t base, int i, int j, typename Op::Coef* C) {
@@ -133,20 +155,20 @@ __device__ __forceinline__ void tile_coefs(const typename Op::Level& L, size_t b
 // p = z + beta p, q = A p, partials of p.q.  beta = rz_new / rz_old, 0 while
 // rz_old is 0: the first iteration, whose p is 0.
 // Bound by memory: it reads z, p and the stencil and writes p and q.
-template <class Op>
+template <class Op, class T>
 __global__ void __launch_bounds__(kThreads)
 dir_q_kernel(Vectors c, typename Op::Level L, int par, int ntx, int nt, int np) {
-  __shared__ double u[kHN];
+  __shared__ double u[T::HN];
   const int b = blockIdx.y, nx = L.nx, ny = L.ny;
   const size_t base = size_t(b) * nx * ny;
   const double *z = c.z + base, *po = (par ? c.p[1] : c.p[0]) + base;
   double *pn = (par ? c.p[0] : c.p[1]) + base, *q = c.q + base;
-  double zv[kSlots], pv[kSlots];
+  double zv[T::SLOTS], pv[T::SLOTS];
   auto load = [&](int t) {
-    const int ty = t / ntx, i0 = (t - ty * ntx) * kTX, j0 = ty * kTY;
+    const int ty = t / ntx, i0 = (t - ty * ntx) * T::TX, j0 = ty * T::TY;
 #pragma unroll
-    for (int s = 0; s < kSlots; ++s) {
-      const Slot S = slot(s, i0, j0, nx, ny);
+    for (int s = 0; s < T::SLOTS; ++s) {
+      const Slot S = slot<T>(s, i0, j0, nx, ny);
       zv[s] = z[S.k], pv[s] = po[S.k];
     }
   };
@@ -154,26 +176,26 @@ dir_q_kernel(Vectors c, typename Op::Level L, int par, int ntx, int nt, int np) 
   const double rzn = wave_total(c.part_rz, b, np), rz = c.rz[size_t(par) * c.batch + b];
   const double beta = rz > 0.0 ? rzn / rz : 0.0;
   if (blockIdx.x == 0 && threadIdx.x == 0) c.rz[size_t(1 - par) * c.batch + b] = rzn;
-  const int x = threadIdx.x & (kTX - 1), y0 = kRows * (threadIdx.x / kTX);
+  const int x = threadIdx.x & (T::TX - 1), y0 = kRows * (threadIdx.x / T::TX);
   double pq = 0.0;
   for (int t = first_tile(); t < nt; t += gridDim.x) {
-    const int ty = t / ntx, i0 = (t - ty * ntx) * kTX, j0 = ty * kTY, i = i0 + x;
+    const int ty = t / ntx, i0 = (t - ty * ntx) * T::TX, j0 = ty * T::TY, i = i0 + x;
     typename Op::Coef C[kRows];
     tile_coefs<Op>(L, base, i, j0 + y0, C);
 #pragma unroll
-    for (int s = 0; s < kSlots; ++s) {
-      const Slot S = slot(s, i0, j0, nx, ny);
+    for (int s = 0; s < T::SLOTS; ++s) {
+      const Slot S = slot<T>(s, i0, j0, nx, ny);
       const double v = S.in ? zv[s] + beta * pv[s] : 0.0;
-      if (S.pos < kHN) u[S.pos] = v;
+      if (S.pos < T::HN) u[S.pos] = v;
       if (S.own) pn[S.k] = v;
     }
     __syncthreads();
 #pragma unroll
     for (int y = 0; y < kRows; ++y) {
-      const double v = tile_op<Op>(C[y], u, x, y0 + y);
+      const double v = tile_op<Op, T>(C[y], u, x, y0 + y);
       if (i < nx && j0 + y0 + y < ny) {
         q[size_t(j0 + y0 + y) * nx + i] = v;
-        pq += u[(y0 + y + 1) * kHX + x + 1] * v;
+        pq += u[(y0 + y + 1) * T::HX + x + 1] * v;
       }
     }
     __syncthreads();
@@ -189,11 +211,11 @@ dir_q_kernel(Vectors c, typename Op::Level L, int par, int ntx, int nt, int np) 
 // r -= alpha q, partials of r.r.
 // Bound by memory on level 0 (it reads x, p, r, q, dinv and the stencil and
 // writes x, r and a quarter of them), by latency on the others.
-template <class Op, bool FINE>
+template <class Op, class T, bool FINE>
 __global__ void __launch_bounds__(kThreads)
 restrict_kernel(Vectors c, typename Op::Level L, double* __restrict__ bc_all, size_t fsc, int par, double tol2, int ntx,
                 int nt, int np) {
-  __shared__ double u[kHN], rb[kTX * kTY];
+  __shared__ double u[T::HN], rb[T::TX * T::TY];
   const int b = blockIdx.y, nx = L.nx, ny = L.ny, nxc = (nx + 1) >> 1, nyc = (ny + 1) >> 1;
   const size_t base = size_t(b) * L.fs;
   double* bc = bc_all + size_t(b) * fsc;
@@ -201,12 +223,12 @@ restrict_kernel(Vectors c, typename Op::Level L, double* __restrict__ bc_all, si
   const double* pn = (par ? c.p[0] : c.p[1]) + base;
   double *rn = (par ? c.r[0] : c.r[1]) + base, *xv = c.x + base;
   const double* dinv = L.dinv + base;
-  double rv[kSlots], qv[kSlots], dv[kSlots], px[kSlots], xx[kSlots];
+  double rv[T::SLOTS], qv[T::SLOTS], dv[T::SLOTS], px[T::SLOTS], xx[T::SLOTS];
   auto load = [&](int t) {
-    const int ty = t / ntx, i0 = (t - ty * ntx) * kTX, j0 = ty * kTY;
+    const int ty = t / ntx, i0 = (t - ty * ntx) * T::TX, j0 = ty * T::TY;
 #pragma unroll
-    for (int s = 0; s < kSlots; ++s) {
-      const Slot S = slot(s, i0, j0, nx, ny);
+    for (int s = 0; s < T::SLOTS; ++s) {
+      const Slot S = slot<T>(s, i0, j0, nx, ny);
       rv[s] = ro[S.k], dv[s] = dinv[S.k];
       if (FINE) {
         qv[s] = q[S.k];
@@ -221,19 +243,19 @@ restrict_kernel(Vectors c, typename Op::Level L, double* __restrict__ bc_all, si
     const bool live = c.rr[b] > tol2 * c.bb[b] && pq > 0.0;
     alpha = live ? rz / pq : 0.0;
   }
-  const int x = threadIdx.x & (kTX - 1), y0 = kRows * (threadIdx.x / kTX);
+  const int x = threadIdx.x & (T::TX - 1), y0 = kRows * (threadIdx.x / T::TX);
   for (int t = first_tile(); t < nt; t += gridDim.x) {
-    const int ty = t / ntx, i0 = (t - ty * ntx) * kTX, j0 = ty * kTY, i = i0 + x;
+    const int ty = t / ntx, i0 = (t - ty * ntx) * T::TX, j0 = ty * T::TY, i = i0 + x;
     typename Op::Coef C[kRows];
     tile_coefs<Op>(L, base, i, j0 + y0, C);
 #pragma unroll
-    for (int s = 0; s < kSlots; ++s) {
-      const Slot S = slot(s, i0, j0, nx, ny);
+    for (int s = 0; s < T::SLOTS; ++s) {
+      const Slot S = slot<T>(s, i0, j0, nx, ny);
       const double r = FINE ? rv[s] - alpha * qv[s] : rv[s];
-      if (S.pos < kHN) u[S.pos] = S.in ? kOmega * dv[s] * r : 0.0;
-      const int py = S.pos / kHX, px_ = S.pos - kHX * py;
+      if (S.pos < T::HN) u[S.pos] = S.in ? kOmega * dv[s] * r : 0.0;
+      const int py = S.pos / T::HX, px_ = S.pos - T::HX * py;
       if (S.own) {
-        rb[(py - 1) * kTX + px_ - 1] = r;
+        rb[(py - 1) * T::TX + px_ - 1] = r;
         if (FINE) {
           xv[S.k] = xx[s] + alpha * px[s];
           rn[S.k] = r;
@@ -245,8 +267,8 @@ restrict_kernel(Vectors c, typename Op::Level L, double* __restrict__ bc_all, si
     double e[kRows];
 #pragma unroll
     for (int y = 0; y < kRows; ++y) {
-      const double v = tile_op<Op>(C[y], u, x, y0 + y);
-      e[y] = (i < nx && j0 + y0 + y < ny) ? rb[(y0 + y) * kTX + x] - v : 0.0;
+      const double v = tile_op<Op, T>(C[y], u, x, y0 + y);
+      e[y] = (i < nx && j0 + y0 + y < ny) ? rb[(y0 + y) * T::TX + x] - v : 0.0;
     }
 #pragma unroll
     for (int y = 0; y < kRows; y += 2) {
@@ -268,24 +290,24 @@ restrict_kernel(Vectors c, typename Op::Level L, double* __restrict__ bc_all, si
 // Coarse correction and post-smoothing of a tile.  FINE: level 0 (b is the CG
 // residual, the result z): partials of r.z, and block 0 stores r.r; start: also
 // as that of the right-hand side.
-template <class Op, bool FINE>
+template <class Op, class T, bool FINE>
 __global__ void __launch_bounds__(kThreads)
 post_kernel(Vectors c, typename Op::Level L, const double* __restrict__ xc_all, size_t fsc, const double* __restrict__ b_all,
             double* __restrict__ t_all, int start, int ntx, int nt, int np) {
-  __shared__ double u[kHN];
+  __shared__ double u[T::HN];
   const int b = blockIdx.y, nx = L.nx, ny = L.ny, nxc = (nx + 1) >> 1;
   const size_t base = size_t(b) * L.fs;
   const double *bf = b_all + base, *dinv = L.dinv + base, *xc = xc_all + size_t(b) * fsc;
   double* out = t_all + base;
-  const int x = threadIdx.x & (kTX - 1), y0 = kRows * (threadIdx.x / kTX);
+  const int x = threadIdx.x & (T::TX - 1), y0 = kRows * (threadIdx.x / T::TX);
   double rz = 0.0;
   for (int t = first_tile(); t < nt; t += gridDim.x) {
-    const int ty = t / ntx, i0 = (t - ty * ntx) * kTX, j0 = ty * kTY, i = i0 + x;
-    double bv[kSlots], dv[kSlots], cv[kSlots];
+    const int ty = t / ntx, i0 = (t - ty * ntx) * T::TX, j0 = ty * T::TY, i = i0 + x;
+    double bv[T::SLOTS], dv[T::SLOTS], cv[T::SLOTS];
 #pragma unroll
-    for (int s = 0; s < kSlots; ++s) {
-      const Slot S = slot(s, i0, j0, nx, ny);
-      const int py = S.pos / kHX, jj = j0 - 1 + py, ii = i0 - 1 + S.pos - kHX * py;
+    for (int s = 0; s < T::SLOTS; ++s) {
+      const Slot S = slot<T>(s, i0, j0, nx, ny);
+      const int py = S.pos / T::HX, jj = j0 - 1 + py, ii = i0 - 1 + S.pos - T::HX * py;
       bv[s] = bf[S.k], dv[s] = dinv[S.k], cv[s] = xc[S.in ? (jj >> 1) * nxc + (ii >> 1) : 0];
     }
     typename Op::Coef C[kRows];
@@ -297,15 +319,15 @@ post_kernel(Vectors c, typename Op::Level L, const double* __restrict__ xc_all, 
       bo[y] = bf[size_t(jc) * nx + ic], dn[y] = dinv[size_t(jc) * nx + ic];
     }
 #pragma unroll
-    for (int s = 0; s < kSlots; ++s) {
-      const Slot S = slot(s, i0, j0, nx, ny);
-      if (S.pos < kHN) u[S.pos] = S.in ? kOmega * dv[s] * bv[s] + cv[s] : 0.0;
+    for (int s = 0; s < T::SLOTS; ++s) {
+      const Slot S = slot<T>(s, i0, j0, nx, ny);
+      if (S.pos < T::HN) u[S.pos] = S.in ? kOmega * dv[s] * bv[s] + cv[s] : 0.0;
     }
     __syncthreads();
 #pragma unroll
     for (int y = 0; y < kRows; ++y) {
-      const double v = tile_op<Op>(C[y], u, x, y0 + y);
-      const double w = u[(y0 + y + 1) * kHX + x + 1] + kOmega * dn[y] * (bo[y] - v);
+      const double v = tile_op<Op, T>(C[y], u, x, y0 + y);
+      const double w = u[(y0 + y + 1) * T::HX + x + 1] + kOmega * dn[y] * (bo[y] - v);
       if (i < nx && j0 + y0 + y < ny) {
         out[size_t(j0 + y0 + y) * nx + i] = w;
         if (FINE) rz += bo[y] * w;
@@ -542,32 +564,47 @@ struct Levels {
     return hipGetLastError();
   }
 
+  // f with the tile of a level
+  template <typename F>
+  static void with_tile(const Level& L, F f) {
+    switch (tile_width(L.nx, L.ny)) {
+      case kNarrowTile: return f(Tile<kNarrowTile>());
+      case kFlatTile: return f(Tile<kFlatTile>());
+      default: return f(Tile<kSquareTile>());
+    }
+  }
   // z = V-cycle of the residual, after the CG update (not at the start); partials of r.z
   void vcycle(const Vectors& c, int par, double tol2, bool start, hipStream_t st) const {
     const int np = blocks(lv[0].nx, lv[0].ny);
     auto grid = [&](const Level& L) { return dim3(unsigned(blocks(L.nx, L.ny)), unsigned(c.batch)); };
     for (int l = 0; l < tail; ++l) {
       const Level &L = lv[l], &C = lv[l + 1];
-      const int ntx = tiles_x(L.nx), nt = tiles(L.nx, L.ny);
-      if (l == 0 && !start)
-        hipLaunchKernelGGL((restrict_kernel<Op, true>), grid(L), dim3(kThreads), 0, st, c, L, C.b, C.fs, par, tol2, ntx,
-                           nt, np);
-      else
-        hipLaunchKernelGGL((restrict_kernel<Op, false>), grid(L), dim3(kThreads), 0, st, c, L, C.b, C.fs, par, tol2, ntx,
-                           nt, np);
+      const int ntx = tiles_x(L.nx, L.ny), nt = tiles(L.nx, L.ny);
+      with_tile(L, [&](auto t) {
+        using T = decltype(t);
+        if (l == 0 && !start)
+          hipLaunchKernelGGL((restrict_kernel<Op, T, true>), grid(L), dim3(kThreads), 0, st, c, L, C.b, C.fs, par, tol2,
+                             ntx, nt, np);
+        else
+          hipLaunchKernelGGL((restrict_kernel<Op, T, false>), grid(L), dim3(kThreads), 0, st, c, L, C.b, C.fs, par, tol2,
+                             ntx, nt, np);
+      });
     }
     const Tail<Op> T = tail_args();
     const size_t lds = tail_lds<Op>(tail_m);
     hipLaunchKernelGGL((tail_kernel<Op>), dim3(c.batch), dim3(kTailThreads), lds, st, T);
     for (int l = tail - 1; l >= 0; --l) {
       const Level &L = lv[l], &C = lv[l + 1];
-      const int ntx = tiles_x(L.nx), nt = tiles(L.nx, L.ny);
-      if (l == 0)
-        hipLaunchKernelGGL((post_kernel<Op, true>), grid(L), dim3(kThreads), 0, st, c, L, C.t, C.fs, c.r[par ? 0 : 1], c.z,
-                           start ? 1 : 0, ntx, nt, np);
-      else
-        hipLaunchKernelGGL((post_kernel<Op, false>), grid(L), dim3(kThreads), 0, st, c, L, C.t, C.fs, L.b, L.t, 0, ntx,
-                           nt, np);
+      const int ntx = tiles_x(L.nx, L.ny), nt = tiles(L.nx, L.ny);
+      with_tile(L, [&](auto t) {
+        using T = decltype(t);
+        if (l == 0)
+          hipLaunchKernelGGL((post_kernel<Op, T, true>), grid(L), dim3(kThreads), 0, st, c, L, C.t, C.fs,
+                             c.r[par ? 0 : 1], c.z, start ? 1 : 0, ntx, nt, np);
+        else
+          hipLaunchKernelGGL((post_kernel<Op, T, false>), grid(L), dim3(kThreads), 0, st, c, L, C.t, C.fs, L.b, L.t, 0,
+                             ntx, nt, np);
+      });
     }
   }
   // After x = p[0] = 0, r[0] = the right-hand side, rz[0] = 0 and the partials
@@ -579,8 +616,10 @@ struct Levels {
   hipError_t iteration(const Vectors& c, int par, double tol2, hipStream_t st) const {
     const Level& L = lv[0];
     const int np = blocks(L.nx, L.ny);
-    hipLaunchKernelGGL((dir_q_kernel<Op>), dim3(np, c.batch), dim3(kThreads), 0, st, c, L, par, tiles_x(L.nx),
-                       tiles(L.nx, L.ny), np);
+    with_tile(L, [&](auto t) {
+      hipLaunchKernelGGL((dir_q_kernel<Op, decltype(t)>), dim3(np, c.batch), dim3(kThreads), 0, st, c, L, par,
+                         tiles_x(L.nx, L.ny), tiles(L.nx, L.ny), np);
+    });
     vcycle(c, par, tol2, false, st);
     return hipGetLastError();
   }
