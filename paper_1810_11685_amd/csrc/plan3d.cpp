@@ -541,26 +541,23 @@ qpat_status reserve3(qpat_plan3d P, int count) {
   return QPAT_OK;
 }
 
-// Launch shape for b vectors on automatic shape: 8-line row blocks while
+// Launch shape for b vectors on automatic shape (the one that
+// qpat3d_get_tiles reports for b = 1).  FFT axes: 8-line row blocks while
 // 16-line ones would give fewer than two blocks per CU, and 1024-thread plane
 // blocks while the plane launches give at most one block per CU (more lines
 // and threads per block only lengthen each block's chain of dependent FFT
 // stages then); 16 lines (the plan's rows) and 512 threads otherwise.
+// Axes transformed as matrix products: four waves (one per SIMD) a block, and
+// one tile of the matrix instruction (16 lines) a row block, but half a tile
+// while that gives at most one block per CU.  A J^T J v of 31 steps, us, 16 ->
+// 8 lines: 24^3 1760 -> 1720, 60 x 48 x 40 2822 -> 2740, 53 x 24 x 24 x 2 2177 ->
+// 2083, 32^3 x 2 (256 blocks of 8) 2294 -> 2255; 33^3 x 2 (274) 2367 -> 2416, 53^3
+// 3062 -> 3195, 53^3 x 4 4831 -> 5684.
 void auto_shape3(const Medium3& base, int b, Medium3& m) {
   m.rt = size_t(b) * ((base.nlines + base.rt - 1) / base.rt) < size_t(2) * kCus ? std::min(8, base.rt) : base.rt;
   m.rthr = 256;
   m.pthr = size_t(3) * b * base.ctiles <= size_t(kCus) ? 1024 : 512;
-}
-
-// Axes transformed as matrix products have their own: one tile of the matrix
-// instruction (16 lines) a row block, four waves (one per SIMD) a block.  The
-// shape that qpat3d_get_tiles names on automatic shape is the one above, which
-// these launches replace.
-void dense_shape3(const Medium3& base, Medium3& m) {
-  if (dense3(base.nx)) {
-    m.rt = 16;
-    m.rthr = 256;
-  }
+  if (dense3(base.nx)) m.rt = size_t(b) * ((base.nlines + 7) / 8) <= size_t(kCus) ? 8 : 16;
   if (dense3_plane(base.ny, base.nz)) m.pthr = 256;
 }
 
@@ -570,10 +567,7 @@ qpat_status exec3(qpat_plan3d P, int b, Exec3** out) {
   if (it == P->execs.end()) {
     std::unique_ptr<Exec3> E(new Exec3());
     E->L.m = P->med;
-    if (P->auto_shape) {
-      auto_shape3(P->med, b, E->L.m);
-      dense_shape3(P->med, E->L.m);
-    }
+    if (P->auto_shape) auto_shape3(P->med, b, E->L.m);
     E->L.w0 = P->w0;
     E->L.wstride = (long long)P->item_bytes;
     E->L.nitems = b;
