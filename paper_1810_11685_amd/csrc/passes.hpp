@@ -602,24 +602,23 @@ __device__ __forceinline__ float2* fft_fused_pairs(float2* a, float2* b, int nli
   else return fft_stages<N, false, LS, 1, NST, R>(o, r, nlines, tw);
 }
 
-// FFT of `nlines` lines, same contract as fft_lines; row lines have stride
-// lstride(n), column lines (COL) col_lstride(n).  NF != 0: an instance for lines
-// of length NF (n == NF), which carries that compile-time plan only; IP: its
-// stages run in place in a (b unused).  NF == 0: an instance for several
+// FFT of `nlines` row lines, same contract as fft_lines.  NF != 0: an instance
+// for lines of length NF (n == NF), which carries that compile-time plan only; IP:
+// its stages run in place in a (b unused).  NF == 0: an instance for several
 // lengths, with MIX all of them (a table launch), else 8 to 24 only.  Each length
 // keeps its compile-time plan in such a launch: one launch set over grids of
 // 96^2, 128^2 and 192^2, J^T J v of 40 to 50 steps, 5.64 ms with run-time plans
 // for the rows, now 4.59; 768^2, 512^2 and 96^2 8.59, now 7.15.
-template <bool COL, int NF, bool IP, bool MIX>
+template <int NF, bool IP, bool MIX>
 __device__ __forceinline__ float2* fft_any(float2* a, float2* b, int nlines, int n, int ls, uint32_t rad,
                                            int nst, const float2* tw) {
   if constexpr (NF != 0) {
-    if constexpr (IP) return fft_c_ip<NF, COL ? col_lstride(NF) : lstride(NF), 0, 1>(a, nlines, tw);
-    else return fft_c<NF, COL ? col_lstride(NF) : lstride(NF), 0, 1>(a, b, nlines, tw);
+    if constexpr (IP) return fft_c_ip<NF, lstride(NF), 0, 1>(a, nlines, tw);
+    else return fft_c<NF, lstride(NF), 0, 1>(a, b, nlines, tw);
   } else {
     if constexpr (MIX) {
 #define QPAT_FFT_CASE(N) \
-  case N: return fft_c<N, COL ? col_lstride(N) : lstride(N), 0, 1>(a, b, nlines, tw);
+  case N: return fft_c<N, lstride(N), 0, 1>(a, b, nlines, tw);
       switch (n) {
         QPAT_FOR_LENGTHS(QPAT_FFT_CASE)
         default: break;
@@ -1282,7 +1281,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     put_pair<NF>(S, bufA, M);
     if constexpr (!TG) put_tw(TW, twl, nx);
     __syncthreads();
-    float2* r = fft_any<false, NF, IP, !U>(bufA, bufB, rt, nx, LS, M.radx, M.nstx, tw);
+    float2* r = fft_any<NF, IP, !U>(bufA, bufB, rt, nx, LS, M.radx, M.nstx, tw);
     float2* o = other(r, bufA, bufB);
     // all LDS reads of the loop first: its LDS writes go to the other buffer,
     // which the compiler cannot tell, so an interleaved loop waits per element
@@ -1310,7 +1309,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
       }
     }
     __syncthreads();
-    r = fft_any<false, NF, IP, !U>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
+    r = fft_any<NF, IP, !U>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
     store_pair_spectra<NF, TG>(r, M, W.s0, W.s1, tile);
   } else if constexpr (FZ) {
     // RM_FZ instances of the lossy density passes (forward eq num-rho and its
@@ -1594,7 +1593,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     float2* r = nullptr;
     float2* o = bufA;
     if (!skip) {
-      r = fft_any<false, NF, IP, !U>(bufA, bufB, rt, nx, LS, M.radx, M.nstx, tw);
+      r = fft_any<NF, IP, !U>(bufA, bufB, rt, nx, LS, M.radx, M.nstx, tw);
       o = other(r, bufA, bufB);
     }
     float2 zr[kMaxPer];
@@ -1645,12 +1644,12 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     if constexpr (BM == RM_F2L) taps_put(T, false);
     __syncthreads();
     if constexpr (BM == RM_F2) {
-      r = fft_any<false, NF, IP, !U>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
+      r = fft_any<NF, IP, !U>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
       store_rowpair_spectra<NF, TG>(r, M, W.s0, tile);
       store_rowpair_spectra<NF, TG>(r + (rt / 2) * LS, M, W.s1, tile);
     } else {
       if (!(flags & FL_NO_SENSORS)) sensor_partials(M, T, o, y0, W.part, n + 1);
-      r = fft_any<false, NF, IP, !U>(o, other(o, bufA, bufB), rt / 2, nx, LS, M.radx, M.nstx, tw);
+      r = fft_any<NF, IP, !U>(o, other(o, bufA, bufB), rt / 2, nx, LS, M.radx, M.nstx, tw);
       store_rowpair_spectra<NF, TG>(r, M, W.s0, tile);
     }
   } else if constexpr (BM == RM_F3) {
@@ -1680,7 +1679,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     if constexpr (!TG) put_tw(TW, twl, nx);
     __syncthreads();
     taps_fetch(T, M, nullptr, 0);
-    float2* r = fft_any<false, NF, IP, !U>(bufA, bufB, rt, nx, LS, M.radx, M.nstx, tw);
+    float2* r = fft_any<NF, IP, !U>(bufA, bufB, rt, nx, LS, M.radx, M.nstx, tw);
     float2* o = other(r, bufA, bufB);
     float ysr[kMaxPer], yur[kMaxPer];
     FOR_K {
@@ -1712,7 +1711,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     taps_put(T, false);
     __syncthreads();
     if (!(flags & FL_NO_SENSORS)) sensor_partials(M, T, o, y0, W.part, n + 1);
-    r = fft_any<false, NF, IP, !U>(o, other(o, bufA, bufB), rt / 2, nx, LS, M.radx, M.nstx, tw);
+    r = fft_any<NF, IP, !U>(o, other(o, bufA, bufB), rt / 2, nx, LS, M.radx, M.nstx, tw);
     store_rowpair_spectra<NF, TG>(r, M, W.s0, tile);
   } else if constexpr (BM == RM_A1 || BM == RM_A1L) {
     // transpose of eqs num-m and num-p: p* += M^T r_{n+1}; q = c^2 p*
@@ -1775,7 +1774,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     nodes_fetch(T, M);
     float2* r = bufA;
     if (!first) {
-      r = fft_any<false, NF, IP, !U>(bufA, bufB, half, nx, LS, M.radx, M.nstx, tw);
+      r = fft_any<NF, IP, !U>(bufA, bufB, half, nx, LS, M.radx, M.nstx, tw);
       // p* = -(grad_x^- g_x + grad_y^- g_y): negate the (conjugated) inverse
 #pragma unroll 4
       for (int it = threadIdx.x; it < half * LS; it += B) {
@@ -1828,11 +1827,11 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     }
     __syncthreads();
     if constexpr (BM == RM_A1) {
-      r = fft_any<false, NF, IP, !U>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
+      r = fft_any<NF, IP, !U>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
       store_rowpair_spectra<NF, TG>(r, M, W.s0, tile);
       store_rowpair_spectra<NF, TG>(r + half * LS, M, W.s1, tile);
     } else if (n != -1) {
-      r = fft_any<false, NF, IP, !U>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
+      r = fft_any<NF, IP, !U>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
       store_pair_spectra<NF, TG>(r, M, W.s0, W.s1, tile);
     }
   } else if constexpr (BM == RM_A2) {
@@ -1873,7 +1872,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     put_rowpair<NF>(S1, bufA + (rt / 2) * LS, M);
     if constexpr (!TG) put_tw(TW, twl, nx);
     __syncthreads();
-    float2* r = fft_any<false, NF, IP, !U>(bufA, bufB, rt, nx, LS, M.radx, M.nstx, tw);
+    float2* r = fft_any<NF, IP, !U>(bufA, bufB, rt, nx, LS, M.radx, M.nstx, tw);
     float2* o = other(r, bufA, bufB);
     float ydr[kMaxPer], yar[kMaxPer];
     FOR_K {
@@ -1906,7 +1905,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     }
     __syncthreads();
     if (n != -1) {
-      r = fft_any<false, NF, IP, !U>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
+      r = fft_any<NF, IP, !U>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
       store_pair_spectra<NF, TG>(r, M, W.s0, W.s1, tile);
     }
   } else if constexpr (BM == RM_A3) {
@@ -1933,7 +1932,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     put_pair<NF>(S, bufA, M);
     if constexpr (!TG) put_tw(TW, twl, nx);
     __syncthreads();
-    float2* r = fft_any<false, NF, IP, !U>(bufA, bufB, rt, nx, LS, M.radx, M.nstx, tw);
+    float2* r = fft_any<NF, IP, !U>(bufA, bufB, rt, nx, LS, M.radx, M.nstx, tw);
     float2* o = other(r, bufA, bufB);
     float2 zr[kMaxPer];
     FOR_K {
@@ -1959,7 +1958,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
       }
     }
     __syncthreads();
-    r = fft_any<false, NF, IP, !U>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
+    r = fft_any<NF, IP, !U>(o, other(o, bufA, bufB), rt, nx, LS, M.radx, M.nstx, tw);
     store_pair_spectra<NF, TG>(r, M, W.s0, W.s1, tile);
   } else if constexpr (BM == RM_FWD1) {
     const float* src = X.in;
@@ -1982,7 +1981,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     }
     if constexpr (!TG) put_tw(TW, twl, nx);
     __syncthreads();
-    float2* r = fft_any<false, NF, IP, !U>(bufA, bufB, rt / 2, nx, LS, M.radx, M.nstx, tw);
+    float2* r = fft_any<NF, IP, !U>(bufA, bufB, rt / 2, nx, LS, M.radx, M.nstx, tw);
     store_rowpair_spectra<NF, TG>(r, M, W.s0, tile);
   } else if constexpr (BM == RM_INV1) {
     RowPairRegs S0;
@@ -1992,7 +1991,7 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     put_rowpair<NF>(S0, bufA, M);
     if constexpr (!TG) put_tw(TW, twl, nx);
     __syncthreads();
-    float2* r = fft_any<false, NF, IP, !U>(bufA, bufB, rt / 2, nx, LS, M.radx, M.nstx, tw);
+    float2* r = fft_any<NF, IP, !U>(bufA, bufB, rt / 2, nx, LS, M.radx, M.nstx, tw);
     float* dst = X.out;
 #pragma unroll 4
     for (int it = threadIdx.x; it < tot; it += B) {
@@ -2036,9 +2035,9 @@ __device__ constexpr int kColCode[kColModes] = {
 __device__ constexpr int kColIn[kColModes] = {1, 2, 2, 2, 2, 1};
 __device__ constexpr int kColOut[kColModes] = {2, 2, 2, 2, 1, 1};
 
-// Column pass for any supported line length (runtime or compile-time FFT
-// plan): the tile goes through LDS between every phase.
-template <int CM, int NF, bool TG>
+// Column pass of the lengths without a compile-time plan (8 to 24): the tile
+// goes through LDS between every phase.
+template <int CM>
 __device__ __forceinline__ void col_generic(const Medium& M, const Work& W, int tile, int mcode, float2* lds) {
   constexpr int nin = kColIn[CM], nout = kColOut[CM];
   const int ny = M.ny, nxh = M.nxh, ct = M.ct, ls = col_lstride(ny);
@@ -2047,8 +2046,7 @@ __device__ __forceinline__ void col_generic(const Medium& M, const Work& W, int 
   const int nsl = 2;
   float2* bufA = lds;
   float2* bufB = lds + nsl * ct * ls;
-  float2* const twl = lds + 2 * nsl * ct * ls;
-  const float2* const tw = TG ? static_cast<const float2*>(M.twy) : twl;
+  float2* const tw = lds + 2 * nsl * ct * ls;
   // which tables this launch uses
   int xcode = 0, ycode = 0;
   bool frac = false, labs = false;
@@ -2083,7 +2081,7 @@ __device__ __forceinline__ void col_generic(const Medium& M, const Work& W, int 
     }
   }
   TwRegsK<kColPer> TW;  // ny <= kColPer * B
-  if constexpr (!TG) fetch_tw(TW, M.twy, ny);
+  fetch_tw(TW, M.twy, ny);
   const int tot = ct * ny;
   MultPre P[kColPer];
 #pragma unroll
@@ -2114,9 +2112,9 @@ __device__ __forceinline__ void col_generic(const Medium& M, const Work& W, int 
       bufA[mul24((f ? ct : 0) + c, ls) + px(ky)] = tv[k];
     }
   }
-  if constexpr (!TG) put_tw(TW, twl, ny);
+  put_tw(TW, tw, ny);
   __syncthreads();
-  float2* r = fft_any<true, 0, false, false>(bufA, bufB, nin * ct, ny, ls, M.rady, M.nsty, tw);
+  float2* r = fft_lines(bufA, bufB, nin * ct, ny, ls, M.rady, M.nsty, tw);
   float2* o = other(r, bufA, bufB);
 #pragma unroll
   for (int k = 0; k < kColPer; ++k) {
@@ -2176,7 +2174,7 @@ __device__ __forceinline__ void col_generic(const Medium& M, const Work& W, int 
     }
   }
   __syncthreads();
-  r = fft_any<true, 0, false, false>(o, other(o, bufA, bufB), nout * ct, ny, ls, M.rady, M.nsty, tw);
+  r = fft_lines(o, other(o, bufA, bufB), nout * ct, ny, ls, M.rady, M.nsty, tw);
   for (unsigned it = threadIdx.x; it < nout * ncol; it += B) {
     const bool f = it >= ncol;
     const unsigned rem = f ? it - ncol : it, w = rem & (rc - 1), ty = rem >> lsh;
@@ -2611,7 +2609,7 @@ col_kernel(const Launch L, int ntile, int chunk, int mcode_arg, int n) {
       }
     }
 #undef QPAT_COL_CASE
-    col_generic<CM, NF, TG>(M, W, tile, mcode, lds);
+    col_generic<CM>(M, W, tile, mcode, lds);
   }
 }
 

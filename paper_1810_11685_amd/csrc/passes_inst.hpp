@@ -17,32 +17,42 @@ static hipError_t allow_fn(K* k, size_t bytes) {
                              int(bytes));
 }
 
+// Whether the RM_FZ instances exist, by where the twiddles are: with radix-4 ends
+// the fused update is only built on LDS twiddles.
+template <int N>
+constexpr bool row_fused(bool tg) {
+  return row_fusable<N>() && (plan_radix(N, 0) > 4 || !tg);
+}
 template <int N>
 bool row_fused_len(bool tg) {
-  return row_fusable<N>() && (plan_radix(N, 0) > 4 || !tg);
+  return row_fused<N>(tg);
+}
+
+template <int MODE, int N>
+static hipError_t launch_row_mode(LaunchKind kind, const Launch& L, int ntile, int chunk, int nblocks, int threads,
+                                  size_t lds, int n, int flags, hipStream_t st) {
+  const dim3 g(nblocks), t(threads);
+  if (kind == LK_TABLE) {
+    hipLaunchKernelGGL((row_kernel<MODE, false, N>), g, t, lds, st, L, ntile, chunk, n, flags);
+  } else if (kind == LK_UNIFORM) {
+    hipLaunchKernelGGL((row_kernel<MODE, true, N>), g, t, lds, st, L, ntile, chunk, n, flags);
+  } else if constexpr ((MODE & RM_FZ) == 0 || row_fused<N>(true)) {
+    hipLaunchKernelGGL((row_kernel<MODE, true, N, true>), g, t, lds, st, L, ntile, chunk, n, flags);
+  } else {
+    return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
 }
 
 template <int N>
 hipError_t launch_row_len(int mode, LaunchKind kind, const Launch& L, int ntile, int chunk, int nblocks, int threads,
                           size_t lds, int n, int flags, hipStream_t st) {
-  const dim3 g(nblocks), t(threads);
-#define QPAT_MODE(m)                                                                                              \
-  case m:                                                                                                         \
-    if (kind == LK_TABLE)                                                                                         \
-      hipLaunchKernelGGL((row_kernel<m, false, N>), g, t, lds, st, L, ntile, chunk, n, flags);                    \
-    else if (kind == LK_UNIFORM)                                                                                  \
-      hipLaunchKernelGGL((row_kernel<m, true, N>), g, t, lds, st, L, ntile, chunk, n, flags);                     \
-    else                                                                                                          \
-      hipLaunchKernelGGL((row_kernel<m, true, N, true>), g, t, lds, st, L, ntile, chunk, n, flags);               \
-    break;
+#define QPAT_MODE(m) \
+  case m: return launch_row_mode<m, N>(kind, L, ntile, chunk, nblocks, threads, lds, n, flags, st);
   if constexpr (row_fusable<N>()) {
-    if (mode & RM_FZ) {
-      if (!row_fused_len<N>(kind == LK_UNIFORM_TG)) return hipErrorInvalidValue;
-      switch (mode) {
-        QPAT_FOR_FUSED_MODES(QPAT_MODE)
-        default: return hipErrorInvalidValue;
-      }
-      return hipGetLastError();
+    switch (mode) {
+      QPAT_FOR_FUSED_MODES(QPAT_MODE)
+      default: break;
     }
   }
   switch (mode) {
@@ -50,7 +60,6 @@ hipError_t launch_row_len(int mode, LaunchKind kind, const Launch& L, int ntile,
     default: return hipErrorInvalidValue;
   }
 #undef QPAT_MODE
-  return hipGetLastError();
 }
 
 template <int N>
@@ -86,15 +95,21 @@ hipError_t allow_lds_len(bool col, size_t bytes) {
 #undef QPAT_MODE
     return e;
   }
-#define QPAT_MODE(m)                                                                \
-  if (e == hipSuccess) e = allow_fn(&row_kernel<m, true, N>, bytes);              \
-  if (e == hipSuccess) e = allow_fn(&row_kernel<m, true, N, true>, bytes);        \
+#define QPAT_MODE(m)                                                     \
+  if (e == hipSuccess) e = allow_fn(&row_kernel<m, true, N>, bytes);   \
   if (e == hipSuccess) e = allow_fn(&row_kernel<m, false, N>, bytes);
+#define QPAT_MODE_TG(m) \
+  if (e == hipSuccess) e = allow_fn(&row_kernel<m, true, N, true>, bytes);
   QPAT_FOR_ROW_MODES(QPAT_MODE)
+  QPAT_FOR_ROW_MODES(QPAT_MODE_TG)
   if constexpr (row_fusable<N>()) {
     QPAT_FOR_FUSED_MODES(QPAT_MODE)
   }
+  if constexpr (row_fused<N>(true)) {
+    QPAT_FOR_FUSED_MODES(QPAT_MODE_TG)
+  }
 #undef QPAT_MODE
+#undef QPAT_MODE_TG
   return e;
 }
 

@@ -58,3 +58,10 @@ def test_kernels_for_several_lengths_keep_their_waves(vgprs):
             seen += 1
             assert waves(v) >= least, (name, v)
     assert seen == 12 + 2 * 9
+
+
+def test_no_kernels_that_no_launch_takes(vgprs):
+    """Fused row kernels on global twiddles exist for the plans with radix-8 ends
+    alone: with radix-4 ends (48, 96, 128, 1024) the launch refuses them."""
+    fused = {m[1] for n in vgprs if (m := re.match(r"void qpat::row_kernel<(?:33|38), true, (\d+), true>", n))}
+    assert fused == {"64", "192", "256", "384", "512", "768"}
