@@ -10,8 +10,8 @@
 // axis: radices 2, 3, 4, 5, 7, 8 as butterflies, any other prime factor as a
 // direct DFT stage, so any length runs without padding.  Axes of 18 to 63 points
 // are transformed as matrix products instead (k3d_dense.hip; dense3 and
-// dense3_plane say which); 49 x 49 planes and 64-point axes have compile-time
-// stages.
+// dense3_plane say which); lengths of two equal stages have kernels of their own
+// (staged3).
 #include "k3d_device.hpp"
 
 namespace qpat3 {
@@ -290,7 +290,7 @@ __device__ __forceinline__ float2* fft_axis(float2* a, float2* b, const LineMap 
   if constexpr (AX == 0) {
     return fft_axis_rt<INV>(a, b, m, P, tw);
   } else {
-    constexpr int R = AX == 49 ? 7 : 8;
+    constexpr int R = staged3(AX);
     static_assert(R * R == AX, "two equal stages");
     stage_ct<R, INV, AX, 1>(a, b, m, tw);
     __syncthreads();
@@ -633,9 +633,10 @@ template <int MODE>
 static hipError_t plane_t(const Launch3& L, int ntile, int chunk, int code, int n, size_t lds, hipStream_t st) {
   const dim3 g(chunk * kXcds), t(L.m.pthr);
   // an instance with compile-time stages only when both transformed axes have its length
-  if (L.m.py.n == 49 && L.m.pz.n == 49)
+  const int R = L.m.py.n == L.m.pz.n ? staged3(L.m.py.n) : 0;
+  if (R == 7)
     hipLaunchKernelGGL((plane3_kernel<MODE, 49>), g, t, lds, st, L, ntile, chunk, code, n);
-  else if (L.m.py.n == 64 && L.m.pz.n == 64)
+  else if (R == 8)
     hipLaunchKernelGGL((plane3_kernel<MODE, 64>), g, t, lds, st, L, ntile, chunk, code, n);
   else
     hipLaunchKernelGGL((plane3_kernel<MODE, 0>), g, t, lds, st, L, ntile, chunk, code, n);

@@ -129,12 +129,18 @@ constexpr int kDenseMin = 18, kDenseMax = 63;
 constexpr int kDenseTiles = 2;   // 16-row tiles of outputs q
 constexpr int kDenseSteps = 8;   // steps of four inputs r
 inline __host__ __device__ bool dense3(int n) { return n >= kDenseMin && n <= kDenseMax; }
-// Planes transformed so: both axes in that range, but not 49 x 49, which the
-// compile-time 7 x 7 stages do in less than the matrix products (16 vectors,
-// the divergence pass of the velocities: 27 against 31 us; one vector: 9.1
-// against 9.4; its x-lines are dense: 26.3 against 28.4 and 6.8 against 8.1).
+// Radix of the lengths that FFT kernels of their own transform in two equal
+// stages, 7 x 7 and 8 x 8 (0: none).
+inline __host__ __device__ constexpr int staged3(int n) { return n == 7 * 7 ? 7 : n == 8 * 8 ? 8 : 0; }
+// Planes transformed as matrix products: both axes in the dense range, unless both
+// have one such FFT: two radix-7 stages cost as much as the products at up to four
+// vectors and less above (a J^T J v of 31 steps, FFT / products: 49^3 x 1 2759 / 2762
+// us, x 4 4163 / 4112, x 8 5385 / 5981, x 16 8644 / 9630; 30 x 49 x 49 x 16 5363 / 6035).
+// Radix 5 has too little in a stage: 25^3 x 1 1830 / 1753, x 16 2307 / 2259.  x-lines
+// take the products at 49 too: a pass of one vector 6.8 us against 8.1, of 16 26.3
+// against 28.4.
 inline __host__ __device__ bool dense3_plane(int ny, int nz) {
-  return dense3(ny) && dense3(nz) && !(ny == 49 && nz == 49);
+  return dense3(ny) && dense3(nz) && !(ny == nz && staged3(ny));
 }
 // length classes of the kernels and their steps of four inputs
 inline __host__ __device__ constexpr int dense3_class(int n) { return n <= 31 ? 0 : n <= 33 ? 1 : n <= 49 ? 2 : 3; }
