@@ -68,16 +68,22 @@ SCOPE_BYTES = {0: 12, 1: 40, 2: 16, 3: 36, 4: 16, 5: 32,
 KERNEL_OF_PASS = {4: "col_fraclap", 7: "col_fraclap"}
 
 
-# Algorithmic HBM bytes per FEM node of one conjugate-gradient iteration of
-# the optical solve (FP64).  CG: A p reads p and the two elemental
-# coefficients of the pixel it owns (8 + 32) and writes q (8); the update
-# reads x, p, r, q (32) and writes x, r (16); r.z reads r, z (16); the new
-# direction reads z, p (16) and writes p (8).  V-cycle, per node of a level
-# (the first sweep's x = om dinv b is recomputed, not stored): the
-# restriction reads b, the inverse diagonal and the 4-array stencil (48) and
-# writes a quarter of a coarse value (2); correction and post-sweep read the
-# same (48) and a quarter of a coarse value (2) and write t (8).  The levels
-# add up to 4/3 of the fine grid's nodes.
+# HBM bytes per FEM node of one conjugate-gradient iteration of the optical
+# solve (FP64), as its launches move them.  Level 0: direction and product read
+# z, p and the 4-array stencil (48) and write p, q (16); the update with the first
+# restriction reads x, p, r, q, the inverse diagonal and the stencil (72) and
+# writes x, r and a quarter of a coarse value (18); correction and post-sweep read
+# r, the inverse diagonal, the stencil (48) and a quarter of a coarse value (2)
+# and write z (8).  The other levels, a third of level 0's nodes in all, as if
+# none of them were in LDS: 50 down (right-hand side, inverse diagonal, stencil,
+# a quarter of a coarse value) and 58 up.
+OPT_MOVED_BYTES_PER_NODE_ITER = 64.0 + 90.0 + 58.0 + (50.0 + 58.0) / 3.0
+# The same iteration with every step on its own, for a rate that compares
+# over versions however the steps are fused.  CG: A p reads p and the two
+# elemental coefficients of a node's pixel (8 + 32) and writes q (8); the update
+# reads x, p, r, q (32) and writes x, r (16); r.z reads r, z (16); the direction
+# reads z, p (16) and writes p (8).  V-cycle: 50 down and 58 up on 4/3 of the
+# fine grid's nodes.
 OPT_CG_BYTES = 48.0 + 48.0 + 16.0 + 24.0
 OPT_VCYCLE_BYTES = (50.0 + 58.0) * 4.0 / 3.0
 OPT_BYTES_PER_NODE_ITER = OPT_CG_BYTES + OPT_VCYCLE_BYTES
@@ -589,8 +595,8 @@ def main():
         torch.cuda.empty_cache()
 
     # ------------------------------------------------------------ optical operators
-    # The diffusion-approximation solve (FP64 Jacobi-CG on the grid-matched P1
-    # mesh) for N_q = 4 illuminations (one per side), on the paper's 2-D
+    # The diffusion-approximation solve (FP64 CG with a multigrid V-cycle on the
+    # grid-matched P1 mesh) for N_q = 4 illuminations (one per side), on the paper's 2-D
     # data-generation grid (128^2 pixels of 78.1 um) and on the headline
     # 512^2 grid; then one composite J dX and J^* r on the headline workload.
     if not args.no_optical:
@@ -615,16 +621,19 @@ def main():
                 sync()
                 t_j = time.perf_counter() - t
             nn_o = (n_o + 1) ** 2
-            gbs = OPT_BYTES_PER_NODE_ITER * nn_o * 4 * its / t_f / 1e9
+            rate = nn_o * 4 * its / t_f / 1e9   # node iterations a nanosecond
+            gbs = OPT_MOVED_BYTES_PER_NODE_ITER * rate
             runs[f"{n_o}"] = {"grid": [n_o, n_o], "illuminations": 4, "forward_s": round(t_f, 4), "cg_iterations": its,
                               "us_per_iteration": round(t_f / its * 1e6, 2), "jv_s": round(t_j, 4),
-                              "algorithmic_GB_s": round(gbs, 1)}
+                              "algorithmic_GB_s": round(gbs, 1),
+                              "separate_steps_GB_s": round(OPT_BYTES_PER_NODE_ITER * rate, 1)}
             log(f"optical {n_o}^2 x4: forward {t_f * 1e3:.1f} ms ({its} CG iterations, "
                 f"{t_f / its * 1e6:.1f} us each, {gbs:.0f} GB/s), J_o v {t_j * 1e3:.1f} ms")
             del opt
         out["optical"] = {"workload": "P1-FEM diffusion approximation (Robin boundary) on the grid-matched mesh, "
                                       "4 illuminations, FP64 CG preconditioned by a multigrid V-cycle, to 1e-8",
-                          "bytes_per_node_per_iteration": OPT_BYTES_PER_NODE_ITER, "runs": runs}
+                          "bytes_per_node_per_iteration": OPT_MOVED_BYTES_PER_NODE_ITER,
+                          "separate_steps_bytes_per_node_per_iteration": OPT_BYTES_PER_NODE_ITER, "runs": runs}
 
     # ------------------------------------------------------------ persistent launch vs kernel boundaries
     # One exchange step of a single-vector solve (every block writes its share
