@@ -389,9 +389,9 @@ qpat_status qpat_ld_run(qpat_ld ld, const float* data, float* x, const qpat_ld_p
  * [nz][ny][nx] (x fastest), node (k, j, i) at ((i - nx/2) dx, (j - ny/2) dy,
  * (k - nz/2) dz); the PML lies inside the grid on all six faces; the
  * measurement M interpolates trilinearly from the 8 surrounding nodes.
- *  nx, ny, nz  axis lengths in [4, 128]; every prime factor of 11 or more is
- *              transformed by a direct DFT stage (e.g. 33, 37, 49, 53 are
- *              supported); ny * nz <= 4096.
+ *  nx, ny, nz  any axis lengths in [4, 128] (18 to 63 points are transformed as
+ *              matrix products, others by FFT stages, a direct DFT stage for
+ *              every prime factor of 11 or more); ny * nz <= 4096.
  *  dz          spacing along z [m]; sensor_xyz host [ns][3] positions [m].
  *  Other fields as in qpat_params.
  * Work is in FP32 with the medium tables built in FP64 and rounded once.

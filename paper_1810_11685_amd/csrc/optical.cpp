@@ -1,6 +1,6 @@
 // Host side of the optical operators (the qpat_optical_* entry points of
 // include/qpat.h): device state of a batch of problems on one grid-matched
-// mesh, the conjugate-gradient driver with a convergence check every 32
+// mesh, the conjugate-gradient driver with a convergence check every eight
 // iterations, and the forward / J_o / J_o^* / pixel-map calls.
 #include <hip/hip_runtime.h>
 
