@@ -28,31 +28,28 @@ bool row_fused_len(bool tg) {
   return row_fused<N>(tg);
 }
 
-template <int MODE, int N>
-static hipError_t launch_row_mode(LaunchKind kind, const Launch& L, int ntile, int chunk, int nblocks, int threads,
-                                  size_t lds, int n, int flags, hipStream_t st) {
-  const dim3 g(nblocks), t(threads);
-  if (kind == LK_TABLE) {
-    hipLaunchKernelGGL((row_kernel<MODE, false, N>), g, t, lds, st, L, ntile, chunk, n, flags);
-  } else if (kind == LK_UNIFORM) {
-    hipLaunchKernelGGL((row_kernel<MODE, true, N>), g, t, lds, st, L, ntile, chunk, n, flags);
-  } else if constexpr ((MODE & RM_FZ) == 0 || row_fused<N>(true)) {
-    hipLaunchKernelGGL((row_kernel<MODE, true, N, true>), g, t, lds, st, L, ntile, chunk, n, flags);
-  } else {
-    return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
 template <int N>
 hipError_t launch_row_len(int mode, LaunchKind kind, const Launch& L, int ntile, int chunk, int nblocks, int threads,
                           size_t lds, int n, int flags, hipStream_t st) {
-#define QPAT_MODE(m) \
-  case m: return launch_row_mode<m, N>(kind, L, ntile, chunk, nblocks, threads, lds, n, flags, st);
+  const dim3 g(nblocks), t(threads);
+#define QPAT_MODE(m)                                                                                              \
+  case m:                                                                                                         \
+    if (kind == LK_TABLE)                                                                                         \
+      hipLaunchKernelGGL((row_kernel<m, false, N>), g, t, lds, st, L, ntile, chunk, n, flags);                    \
+    else if (kind == LK_UNIFORM)                                                                                  \
+      hipLaunchKernelGGL((row_kernel<m, true, N>), g, t, lds, st, L, ntile, chunk, n, flags);                     \
+    else if constexpr (((m) & RM_FZ) == 0 || row_fused<N>(true))                                                  \
+      hipLaunchKernelGGL((row_kernel<m, true, N, true>), g, t, lds, st, L, ntile, chunk, n, flags);               \
+    else                                                                                                          \
+      return hipErrorInvalidValue;                                                                                \
+    break;
   if constexpr (row_fusable<N>()) {
-    switch (mode) {
-      QPAT_FOR_FUSED_MODES(QPAT_MODE)
-      default: break;
+    if (mode & RM_FZ) {
+      switch (mode) {
+        QPAT_FOR_FUSED_MODES(QPAT_MODE)
+        default: return hipErrorInvalidValue;
+      }
+      return hipGetLastError();
     }
   }
   switch (mode) {
@@ -60,6 +57,7 @@ hipError_t launch_row_len(int mode, LaunchKind kind, const Launch& L, int ntile,
     default: return hipErrorInvalidValue;
   }
 #undef QPAT_MODE
+  return hipGetLastError();
 }
 
 template <int N>
