@@ -87,8 +87,9 @@ __global__ void __launch_bounds__(kBlock) dot_final(const double* __restrict__ p
 // ---------------------------------------------------------------- launchers
 // Launches pick the kernel instance for their row / column length (lengths
 // with a compile-time plan): uniform launches by the plan's length, table
-// launches by the length all their items share (`len`, 0 when they differ:
-// then the all-length instance, which also serves the short lengths).
+// launches by the length all their items share (`len`, 0 when they differ).
+// The instances without a length: for table launches over several, which hold
+// them all, and for uniform launches of the short ones (8 to 24).
 template <int MODE>
 static hipError_t launch_row_any(const Launch& L, bool uniform, int ntile, int chunk, int nblocks, int threads,
                                  size_t lds, int n, int flags, hipStream_t st) {

@@ -213,7 +213,7 @@ __host__ __device__ constexpr int plan_nst(int n) {
 // stages at both ends (a = 3q + 1: 4 8..8 4) or one radix-4 second stage
 // (a = 3q + 2: 8 4 8..8), so that a plan of two or more stages starts and
 // ends with the same radix where it can (the row passes fuse the boundary
-// stage of two FFTs).  3 2^a with a >= 4: the factor 3 in the middle stage of
+// stage of two FFTs; of the lengths with kernels only 32 = 8 4 cannot).  3 2^a with a >= 4: the factor 3 in the middle stage of
 // three (48: 4 3 4, 96: 4 6 4, 192: 8 3 8, 384: 8 6 8, 768: 8 12 8), so those
 // plans read the same both ways and fuse like the powers of two (with the
 // radix-3 stage last the column passes went through LDS between all phases:
@@ -1317,10 +1317,10 @@ row_kernel(const Launch L, int ntile, int chunk, int n, int flags) {
     // state: only the fused path is compiled, so the first iterates' code does
     // not set these kernels' register count.  The host launches them only for
     // compile-time lengths whose plan fuses (kernels_row_fused).  Plans whose
-    // boundary stage has radix 8 (256, 512) hold one row per work item, the
+    // boundary stage has radix 8 (64, 192 to 768) hold one row per work item, the
     // rows 2l and 2l+1 of a pair in adjacent lanes (fft_fused_pairs); radix-4
-    // ones (128, 1024) two rows per work item (fft_fused2), which is faster
-    // there, and only where the twiddles sit in LDS.
+    // ones (48, 96, 128, 1024) two rows per work item (fft_fused2), which is
+    // faster at 128 and 1024, and only where the twiddles sit in LDS.
     constexpr bool PAIRS = plan_radix(NF > 0 ? NF : 8, 0) > 4;
     if constexpr (BM == RM_F2 && row_fusable<NF>() && PAIRS) {
       // each row's inverse line in, S and u lines (rows 2l, 2l+1 packed) out

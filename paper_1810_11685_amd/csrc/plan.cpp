@@ -133,8 +133,8 @@ bool threads_ok(int t) { return t == 64 || t == 128 || t == 256 || t == 512; }
 // A row tile of rt rows (rt even, dividing ny) fits the LDS limit and leaves
 // at most kMaxPer pointwise elements per thread.
 bool row_tile_ok(int nx, int ny, int rt, int thr) {
-  // power-of-two columns of 128+ take the fused column pass, which needs the
-  // tile height to divide the first-stage stride (at least ny / 8)
+  // at power-of-two columns of 128+ the fused column pass takes it that the tile
+  // height divides its first-stage stride (at least ny / 8); elsewhere it tests
   const bool fused_cols = ny >= 128 && (ny & (ny - 1)) == 0;
   return rt >= 2 && (rt & (rt - 1)) == 0 && ny % rt == 0 && row_lds_bytes(nx, rt) <= kMaxLds &&
          threads_ok(thr) && rt * nx <= kMaxPer * thr && (!fused_cols || rt <= ny / 8);
