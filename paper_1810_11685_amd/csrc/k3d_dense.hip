@@ -26,11 +26,11 @@
 // Bound: latency of the dependent phases at few vectors (a plane's matrix
 // instructions take 3 us of its 9), the matrix unit and L2 at many.  Microseconds
 // an iterate, one / three / sixteen vectors, FFT stages -> these passes:
-//   53 x 53 x 53  107 / 142 / 477 -> 50 / 66 / 203
+//   53 x 53 x 53  107 / 142 / 477 -> 50 / 65 / 200
 //   60 x 48 x 40   72 /  93 / 215 -> 46 / 63 / 162
-//   48 x 48 x 48   90 / 102 / 259 -> 44 / 52 / 147
-//   32 x 32 x 32   55 /  58 /  99 -> 36 / 38 /  77
-//   24 x 24 x 24   52 /  53 /  68 -> 28 / 29 /  37
+//   48 x 48 x 48   90 / 102 / 259 -> 44 / 52 / 148
+//   32 x 32 x 32   55 /  58 /  99 -> 36 / 38 /  78
+//   24 x 24 x 24   52 /  53 /  68 -> 28 / 28 /  36
 // (shorter than 18 an axis has too few steps for the matrix unit; from 64 the
 // products grow past what the FFT stages take).
 #include "k3d_device.hpp"
@@ -93,6 +93,31 @@ __device__ __forceinline__ void mat_load(Mat<K>& R, const float* __restrict__ t,
 #pragma unroll
   for (int k = 0; k < K / 2; ++k) R.v[k] = p[k * 64 + lane];
 }
+
+// Lanes 32 to 63 of a against lanes 0 to 31 of b (both halves of the wave active).
+__device__ __forceinline__ void half_swap(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void half_swap(float2& a, float2& b) {
+  half_swap(a.x, b.x);
+  half_swap(a.y, b.y);
+}
+
+// The order of a sum.  A smooth field in the middle of the grid is small at r = 0
+// and large towards r = n/2, and its transform at high q is a difference of large
+// terms; a spectrum is large at q = 0.  What a sum loses is its roundings while it
+// is large, so forward transforms add r upwards, inverse ones downwards with the
+// term of r = 0 last, each as two chains, one per half of the steps (two
+// accumulators: half as many roundings in a row, and two independent chains for the
+// matrix unit).  Relative L2 error of d/dx of five blobs, 1e-7: FFT stages / even
+// and odd steps of inputs a quarter of the range apart / so ordered: 31^3 4.6 / 5.9 /
+// 3.9, 53^3 4.4 / 6.8 / 4.0, 60^3 7.3 / 8.2 / 4.0; of white noise, 53^3, 2.5 / 2.1 / 2.1.
+// A J^T J v of 31 steps: 53^3 3.07 -> 3.11 ms, x 16 12.51 -> 12.38.
+// Step i of chain h (0: the half of the small r) of S steps:
+template <int S, bool DOWN>
+__host__ __device__ constexpr int chain_step(int h, int i) { return h * (S / 2) + (DOWN ? S / 2 - 1 - i : i); }
 
 // LDS row stride (floats) of an x-line, with a slot past its end: 4 times an
 // odd number, so that the sixteen lines of a tile start in different banks.
@@ -281,7 +306,7 @@ __global__ void __launch_bounds__(kDenseThreads) row3_dense_kernel(const Launch3
       const float2* sk = src + size_t(k) * specN;
       x0[k] = sk[lo];
 #pragma unroll
-      for (int s = 0; s < S; ++s) b[k][s] = sk[lo + col_off(min(S * g + s + 1, nxh))];
+      for (int s = 0; s < S; ++s) b[k][s] = sk[lo + col_off(min(dense3_input(s, g) + 1, nxh))];
     }
   };
   const int uin = nin * G * MT;
@@ -336,19 +361,20 @@ __global__ void __launch_bounds__(kDenseThreads) row3_dense_kernel(const Launch3
       const int mt = u % MT, fg = u / MT, f = fg / G, grp = fg - f * G;
       float p0 = x0[0].x;
       if constexpr (NSUM == 3) p0 = (x0[0].x + x0[1].x) + x0[2].x;
-      f4 P[2] = {splat(p0), splat(0.f)}, Q[2] = {splat(0.f), splat(0.f)};
+      f4 P[2] = {splat(0.f), splat(0.f)}, Q[2] = {splat(0.f), splat(0.f)};
 #pragma unroll
-      for (int s = 0; s < S; ++s) {
+      for (int k = 0; k < S; ++k) {
+        const int s = chain_step<S, true>(k & 1, k >> 1);
         float2 v = b[0][s];
         if constexpr (NSUM == 3) v = cadd(cadd(b[0][s], b[1][s]), b[2][s]);
-        P[s & 1] = mma(A.c(s), v.x, P[s & 1]);
-        Q[s & 1] = mma(A.s(s), v.y, Q[s & 1]);
+        P[k & 1] = mma(A.c(s), v.x, P[k & 1]);
+        Q[k & 1] = mma(A.s(s), v.y, Q[k & 1]);
       }
       float* row = ldsf + f * FS + (16 * grp + m) * LX;
       const int j = 16 * mt + 4 * g;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float c = P[0][i] + P[1][i], d = Q[0][i] + Q[1][i];
+        const float c = (P[1][i] + P[0][i]) + p0, d = Q[1][i] + Q[0][i];
         row[j + i] = c - d;
         row[nx - j - i] = c + d;   // j = 0: the slot past the line
       }
@@ -407,13 +433,14 @@ __global__ void __launch_bounds__(kDenseThreads) row3_dense_kernel(const Launch3
     const int mt = u % MT, og = u / MT, o = og / G, grp = og - o * G;
     if (MT > 1 && mt != w % MT) mat_load(A, M.dfx, mt, lane);
     const float* row = ldsf + o * FS + (16 * grp + m) * LX;
-    const float *up = row + S * g + 1, *dn = row + (nx - S * g - S);
+    const float *up = row + g + 1, *dn = row + (nx - g - 1);
     f4 P[2] = {splat(row[0]), splat(0.f)}, Q[2] = {splat(0.f), splat(0.f)};
 #pragma unroll
-    for (int s = 0; s < S; ++s) {
-      const float xa = up[s], xm = dn[S - 1 - s];
-      P[s & 1] = mma(A.c(s), xa + xm, P[s & 1]);
-      Q[s & 1] = mma(A.s(s), xa - xm, Q[s & 1]);
+    for (int k = 0; k < S; ++k) {
+      const int s = chain_step<S, false>(k & 1, k >> 1);
+      const float xa = up[dense3_input(s, 0)], xm = dn[-dense3_input(s, 0)];
+      P[k & 1] = mma(A.c(s), xa + xm, P[k & 1]);
+      Q[k & 1] = mma(A.s(s), xa - xm, Q[k & 1]);
     }
     if (MT > 1 && mt != w % MT) mat_load(A, M.dfx, w % MT, lane);
     const int l = l0 + 16 * grp + m;
@@ -433,30 +460,27 @@ __global__ void __launch_bounds__(kDenseThreads) row3_dense_kernel(const Launch3
 
 // ---------------------------------------------------------------- plane pass
 // One row tile of a complex transform: cos and sin products of the real and
-// imaginary parts.  Even and odd steps have accumulators of their own, added at
-// the end: half as many roundings follow one another (60 x 48 x 40, relative L2
-// error of an operator on white noise: 2.00e-7; one chain 2.40e-7; FFT stages
-// 2.11e-7), and eight independent chains keep the matrix unit busy.  One tile
-// at a time, so that this costs no registers.
+// imaginary parts, in two chains (above), eight independent ones in all, which
+// keeps the matrix unit busy.  One tile at a time, so that this costs no registers.
 struct Acc {
   f4 cr, ci, sr, si;
 };
-// e, o: x_r +- x_{n-r} of the steps; mat(s / 2): cos and sin of two steps
-template <int S, typename MatAt>
-__device__ __forceinline__ Acc tile_products(float2 x0, const float2* e, const float2* o, MatAt mat) {
-  Acc a[2] = {{splat(x0.x), splat(x0.y), splat(0.f), splat(0.f)}, {splat(0.f), splat(0.f), splat(0.f), splat(0.f)}};
+// e, o: x_r +- x_{n-r} of the steps
+template <bool DOWN, int S>
+__device__ __forceinline__ Acc tile_products(float2 x0, const float2* e, const float2* o, const Mat<S>& A) {
+  const f4 zero = splat(0.f);
+  Acc a[2] = {{DOWN ? zero : splat(x0.x), DOWN ? zero : splat(x0.y), zero, zero}, {zero, zero, zero, zero}};
 #pragma unroll
-  for (int s = 0; s < S; s += 2) {
-    const f4 A = mat(s / 2);
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      a[h].cr = mma(A[2 * h], e[s + h].x, a[h].cr);
-      a[h].ci = mma(A[2 * h], e[s + h].y, a[h].ci);
-      a[h].sr = mma(A[2 * h + 1], o[s + h].x, a[h].sr);
-      a[h].si = mma(A[2 * h + 1], o[s + h].y, a[h].si);
-    }
+  for (int k = 0; k < S; ++k) {
+    const int h = k & 1, s = chain_step<S, DOWN>(h, k >> 1);
+    a[h].cr = mma(A.c(s), e[s].x, a[h].cr);
+    a[h].ci = mma(A.c(s), e[s].y, a[h].ci);
+    a[h].sr = mma(A.s(s), o[s].x, a[h].sr);
+    a[h].si = mma(A.s(s), o[s].y, a[h].si);
   }
-  return {a[0].cr + a[1].cr, a[0].ci + a[1].ci, a[0].sr + a[1].sr, a[0].si + a[1].si};
+  Acc r = {a[1].cr + a[0].cr, a[1].ci + a[0].ci, a[1].sr + a[0].sr, a[1].si + a[0].si};
+  if (DOWN) r.cr += splat(x0.x), r.ci += splat(x0.y);
+  return r;
 }
 // outputs q and n - q of register i: C -+ i S (forward), the other way inverse
 template <bool INV>
@@ -516,22 +540,24 @@ plane3_dense_kernel(const Launch3 L, int ntile, int chunk, PlaneOps P, int n) {
     const unsigned base = unsigned(min(16 * zt + m, nz - 1) * ny) * unsigned(ct) + unsigned(c);
     x0 = in[base];
     if (ct == 1) {
-      const float2 *up = in + base + (SY * g + 1), *dn = in + base + (ny - SY * g - SY);
+      // (pairs, traded between the lanes before use)
+      const float2 *up = in + base + (2 * g + 1), *dn = in + base + (ny - 2 * g - 2);
 #pragma unroll
       for (int s = 0; s < SY; s += 2) {
-        ld2(up + s, xa[s], xa[s + 1]);
-        ld2(dn + s, xm[SY - 1 - s], xm[SY - 2 - s]);
+        ld2(up + dense3_input(s, 0), xa[s], xa[s + 1]);
+        ld2(dn - dense3_input(s, 0), xm[s + 1], xm[s]);
       }
     } else {
-      const unsigned lo = base + unsigned((SY * g + 1) * ct), hi = base + unsigned((ny - SY * g - 1) * ct);
+      const unsigned r0 = unsigned(dense3_input_y(0, g) + 1);
+      const unsigned lo = base + r0 * unsigned(ct), hi = base + (unsigned(ny) - r0) * unsigned(ct);
 #pragma unroll
       for (int s = 0; s < SY; ++s) {
-        xa[s] = in[lo + unsigned(s * ct)];
-        xm[s] = in[hi - unsigned(s * ct)];
+        xa[s] = in[lo + unsigned(dense3_input(s, 0) * ct)];
+        xm[s] = in[hi - unsigned(dense3_input(s, 0) * ct)];
       }
     }
   };
-  // k-space factors of rows q and n - q of register i, row tile mt, column ky
+  // k-space factors of rows q = dense3_input(4 mt + i, g) and n - q of register i, row tile mt, column ky
   float kf[MZ][4][2];
   float2 one;
   auto sym_load = [&](int kt, int col, int lane) {
@@ -539,12 +565,12 @@ plane3_dense_kernel(const Launch3 L, int ntile, int chunk, PlaneOps P, int n) {
     const float* tab = (cd == OP_LDIS ? M.ldis : cd == OP_LABS ? M.labs : M.kap) + size_t(col) * nl;
     one = cd == OP_DXP ? M.dxp[col] : cd == OP_DXM ? M.dxm[col] : cd == OP_DYP ? M.dyp[ky]
           : cd == OP_DYM ? M.dym[ky] : make_float2(1.f, 0.f);
-    const unsigned lo = unsigned(4 * g * ny + ky), hi = unsigned((nz - 4 * g) * ny + ky);
+    const unsigned lo = unsigned(g * ny + ky), hi = unsigned((nz - g) * ny + ky);
 #pragma unroll
     for (int mt = 0; mt < MZ; ++mt)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const unsigned d = unsigned((16 * mt + i) * ny);
+        const unsigned d = unsigned(dense3_input(4 * mt + i, 0) * ny);
         kf[mt][i][0] = tab[lo + d];
         kf[mt][i][1] = tab[(mt == 0 && i == 0 && g == 0) ? lo : hi - d];   // the mirror of row 0 is row 0
       }
@@ -574,6 +600,10 @@ plane3_dense_kernel(const Launch3 L, int ntile, int chunk, PlaneOps P, int n) {
     for (int zt = w; zt < NTz; zt += nw) {
       const int lane = opaque(tid & 63), g = lane >> 4, m = lane & 15;
       if (c > 0 || zt != w) y_load(zt, c, lane);
+      if (ct == 1) {
+#pragma unroll
+        for (int s = 0; s < SY; s += 2) half_swap(xa[s], xa[s + 1]), half_swap(xm[s], xm[s + 1]);
+      }
       float2 e[SY], o[SY];
 #pragma unroll
       for (int s = 0; s < SY; ++s) e[s] = cadd(xa[s], xm[s]), o[s] = csub(xa[s], xm[s]);
@@ -581,7 +611,7 @@ plane3_dense_kernel(const Launch3 L, int ntile, int chunk, PlaneOps P, int n) {
       float2 *lo = lds2 + z * LY + 4 * g, *hi = lds2 + z * LY + ny - 4 * g;
 #pragma unroll
       for (int mt = 0; mt < MY; ++mt) {
-        const Acc acc = tile_products<SY>(x0, e, o, [&](int k) { return Ay[mt].v[k]; });
+        const Acc acc = tile_products<false>(x0, e, o, Ay[mt]);
         if (z < nz)
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
@@ -599,24 +629,24 @@ plane3_dense_kernel(const Launch3 L, int ntile, int chunk, PlaneOps P, int n) {
       if (c > 0 || kt != w) sym_load(kt, c0 + c, lane);
       const int ky = 16 * kt + m;
       const float2* src = lds2 + min(ky, ny - 1);
-      const float2 *up = src + (SZ * g + 1) * LY, *dn = src + (nz - SZ * g - SZ) * LY;
+      const float2 *up = src + (g + 1) * LY, *dn = src + (nz - g - 1) * LY;
       const float2 z0 = src[0];
 #pragma unroll
       for (int mt = 0; mt < MZ; ++mt) mat_load(Ac[mt], M.dfzc, mt, lane);   // arrives over the z forward products
       float2 e[SZ], o[SZ];
 #pragma unroll
       for (int s = 0; s < SZ; ++s) {
-        const float2 a = up[s * LY], b = dn[(SZ - 1 - s) * LY];
+        const float2 a = up[dense3_input(s, 0) * LY], b = dn[-dense3_input(s, 0) * LY];
         e[s] = cadd(a, b), o[s] = csub(a, b);
       }
       // multiplied rows q and n - q, folded again: the inputs of the inverse
       float2 ei[4 * MZ], oi[4 * MZ];
 #pragma unroll
       for (int mt = 0; mt < MZ; ++mt) {
-        const Acc acc = tile_products<SZ>(z0, e, o, [&](int k) { return Az[mt].v[k]; });
+        const Acc acc = tile_products<false>(z0, e, o, Az[mt]);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const int q = 16 * mt + 4 * g + i;
+          const int q = dense3_input(4 * mt + i, g);
           float2 a, b;
           acc_out<false>(acc, i, a, b);
           a = sym_mul(kf[mt][i][0], q, a);
@@ -630,7 +660,7 @@ plane3_dense_kernel(const Launch3 L, int ntile, int chunk, PlaneOps P, int n) {
       float2 *lo = lds2 + 4 * g * LY + ky, *hi = lds2 + (nz - 4 * g) * LY + ky;
 #pragma unroll
       for (int mt = 0; mt < MZ; ++mt) {
-        const Acc acc = tile_products<4 * MZ>(make_float2(0.f, 0.f), ei, oi, [&](int k) { return Ac[mt].v[k]; });
+        const Acc acc = tile_products<true>(make_float2(0.f, 0.f), ei, oi, Ac[mt]);
         if (ky < ny)
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
@@ -649,18 +679,21 @@ plane3_dense_kernel(const Launch3 L, int ntile, int chunk, PlaneOps P, int n) {
       const int lane = opaque(tid & 63), g = lane >> 4, m = lane & 15;
       const int z = 16 * zt + m;
       const float2* src = lds2 + min(z, nz - 1) * LY;
-      const float2 *up = src + SY * g + 1, *dn = src + (ny - SY * g - SY);
+      const float2 *up = src + 2 * g + 1, *dn = src + (ny - 2 * g - 1);
       const float2 y0 = src[0];
       float2 e[SY], o[SY];
 #pragma unroll
-      for (int s = 0; s < SY; ++s) {
-        const float2 a = up[s], b = dn[SY - 1 - s];
+      for (int s = 0; s < SY; s += 2) {
+        const int d = dense3_input(s, 0);
+        const float2 a = up[d], b = dn[-d], a1 = up[d + 1], b1 = dn[-d - 1];
         e[s] = cadd(a, b), o[s] = csub(a, b);
+        e[s + 1] = cadd(a1, b1), o[s + 1] = csub(a1, b1);
+        half_swap(e[s], e[s + 1]), half_swap(o[s], o[s + 1]);
       }
       float2* dst = out + unsigned(z * ny) * unsigned(ct) + c;
 #pragma unroll
       for (int mt = 0; mt < MY; ++mt) {
-        const Acc acc = tile_products<SY>(y0, e, o, [&](int k) { return Ay[mt].v[k]; });
+        const Acc acc = tile_products<true>(y0, e, o, Ay[mt]);
         if (z < nz) {
           const int j = 16 * mt + 4 * g;   // rows j .. j + 3 and their mirrors
           float2 a[4], b[4];

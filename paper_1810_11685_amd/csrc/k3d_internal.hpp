@@ -147,10 +147,17 @@ inline __host__ __device__ constexpr int dense3_class(int n) { return n <= 31 ? 
 inline __host__ __device__ constexpr int dense3_steps(int cls) { return cls <= 1 ? 4 : cls == 2 ? 6 : 8; }
 // A matrix as the matrix instruction's first operand, [tile][step / 2][lane]
 // [step % 2][cos, sin]: lane l of step s holds row q = 16 tile + l % 16 and
-// input r = S (l / 16) + s + 1 (S steps: a lane's inputs are neighbours).  The
-// chained form takes its inputs from the
-// accumulators of a preceding product (register i of row tile t in step 4 t + i):
-// r = 16 t + 4 (l / 16) + i, from r = 0, which counts half too.  Size in floats:
+// input r = dense3_input(s, l / 16) + 1: the inputs of a step are neighbours and
+// grow over the steps (what a sum loses depends on it, see chain_step in
+// k3d_dense.hip).  The chained form takes its inputs from the accumulators of a preceding product (register i of row tile t
+// in step 4 t + i) with r = dense3_input(4 t + i, l / 16), from r = 0, which counts
+// half too; the rows of that preceding product are in the order that gives this.
+inline __host__ __device__ constexpr int dense3_input(int s, int g) { return 4 * s + g; }
+// The inputs of a y transform, whose lanes load them in pairs (r, r + 1 with
+// r = 8 p + 2 g + 1 for steps 2 p and 2 p + 1) and trade one of each between the
+// halves of the wave: the same inputs a step, in another order of the lanes.
+inline __host__ __device__ constexpr int dense3_input_y(int s, int g) { return 4 * s + (g % 2 * 2 + g / 2); }
+// Size in floats:
 constexpr size_t kDenseTable = size_t(kDenseTiles) * kDenseSteps * 2 * 64;
 static_assert(4 * kDenseTiles == kDenseSteps, "the chained form has four steps a tile");
 

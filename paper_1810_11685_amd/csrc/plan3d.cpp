@@ -353,14 +353,16 @@ qpat_status plan3_build(qpat_plan3d P, const double* c0, const double* rho0) {
   // and opposite sines to the bit.  half: the weight of an input that is its
   // own mirror; other: of the rest (2 and 1 reversed for the inverse x
   // transform, whose inputs are a half spectrum).
-  auto dft = [](int n, bool chained, double other, double half) {
+  enum Form { kPlain, kY, kFeeds, kChained };   // kFeeds: rows in the order of a chained product's inputs
+  auto dft = [](int n, Form form, double other, double half) {
+    const bool chained = form == kChained;
     std::vector<float> t(kDenseTable, 0.f);
     const int S = dense3_steps(dense3_class(n));
     for (int tile = 0; tile < kDenseTiles; ++tile)
       for (int s = 0; s < kDenseSteps; ++s)
         for (int l = 0; l < 64; ++l) {
-          const int q = 16 * tile + l % 16;
-          const int r = chained ? 16 * (s / 4) + 4 * (l / 16) + s % 4 : S * (l / 16) + s + 1;
+          const int q = 16 * tile + (form == kFeeds ? dense3_input(l % 4, l % 16 / 4) : l % 16);
+          const int r = (form == kY ? dense3_input_y(s, l / 16) : dense3_input(s, l / 16)) + (chained ? 0 : 1);
           if (2 * r > n || (!chained && s >= S)) continue;
           const int m = q * r % n, mm = std::min(m, n - m);
           const double w = (r == 0 || 2 * r == n) ? half : other, a = 2.0 * M_PI * double(mm) / double(n);
@@ -371,9 +373,9 @@ qpat_status plan3_build(qpat_plan3d P, const double* c0, const double* rho0) {
         }
     return t;
   };
-  const std::vector<float> dfx = dft(nx, false, 1.0, 0.5), dfxi = dft(nx, false, 2.0, 1.0),
-                           dfy = dft(ny, false, 1.0, 0.5), dfz = dft(nz, false, 1.0, 0.5),
-                           dfzc = dft(nz, true, 1.0, 0.5);
+  const std::vector<float> dfx = dft(nx, kPlain, 1.0, 0.5), dfxi = dft(nx, kPlain, 2.0, 1.0),
+                           dfy = dft(ny, kY, 1.0, 0.5), dfz = dft(nz, kFeeds, 1.0, 0.5),
+                           dfzc = dft(nz, kChained, 1.0, 0.5);
   std::vector<Tap3> taps;
   std::vector<int> toff;
   build_taps3(p, taps, toff);
