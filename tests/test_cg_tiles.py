@@ -23,7 +23,7 @@ int main(int argc, char** argv) {
 def test_tiles_of_strips_are_mostly_inside(tmp_path):
     (tmp_path / "tiles.hip").write_text(DRIVER)
     exe = str(tmp_path / "tiles")
-    subprocess.run([B.hipcc(), "--offload-arch=gfx950", "-std=c++17", "-I", B.CSRC, str(tmp_path / "tiles.hip"), "-o", exe],
+    subprocess.run([B.hipcc(), *B.HIP_FLAGS, "-I", B.CSRC, str(tmp_path / "tiles.hip"), "-o", exe],
                    check=True)
     sizes = [(w, 2000) for w in range(2, 33)] + [(2000, h) for h in range(2, 33)]
     out = subprocess.run([exe, *(str(v) for s in sizes for v in s)], check=True, capture_output=True, text=True).stdout
